@@ -143,7 +143,8 @@ const char* eig_last_error(void);
 size_t eig_ctx_workspace_bytes(const eig_ctx* ctx);
 /* Stencil timing since the last reset: device time from the first to the
  * last stencil launch of every wave (HIP events on the call's stream), the
- * number of stencil launches, the grid-point updates they performed
+ * number of stencil launches (a launch of more than four steps counts as the
+ * four-step launches it stands for), the grid-point updates they performed
  * (sum over solves of nx*nz per step) and their algorithmic HBM bytes (per
  * update: read u^m and u^{m-1}, write u^{m+1}, 8 bytes each; plus 12 bytes
  * of nodal coefficients for EIG_MEDIUM_NODAL).  Waits for the recorded
@@ -218,12 +219,12 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
 int eig_ctx_set_option(eig_ctx* ctx, const char* name, int64_t value);
 /* Reads an option back; "last_variant" gives the stencil variant of the most
  * recent launch.  "temporal_blocking": leapfrog steps per launch for media
- * with rigid edges, 4 (default: the tile and its halo in LDS for four steps,
- * variants 23 depth-only, 24 and 25 nodal), 2 (1 also selects 2), 3
+ * with rigid edges, 4 (default: four or more; depth-only variants 23, eight
+ * steps streamed through registers, and 26 for small launches, four with the
+ * tile and its halo in LDS; nodal variants 24 and 25), 2 (1 also selects 2), 3
  * (depth-only media; nodal media then take two), or 0 for one step; two to
  * four steps per launch keep four field buffers per solve.  Serving engines
- * created while it is 4 take four steps per launch for both media (variants
- * 23, 24); otherwise two for depth-only media and one for nodal media. */
+ * created while it is 4 run those variants for both media; otherwise two for depth-only media and one for nodal media. */
 int eig_ctx_get_option(const eig_ctx* ctx, const char* name, int64_t* value);
 
 /*

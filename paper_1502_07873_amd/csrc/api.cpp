@@ -77,7 +77,7 @@ int tiled_steps_of(const eig_ctx* c, const SolveSpec& sp, const eig_grid& g,
     if (c->forced_variant >= 0 && kVariants[c->forced_variant].medium_kind == mk.kind &&
         !kVariants[c->forced_variant].resident &&
         !(one_step && kVariants[c->forced_variant].steps != 1))
-        steps = kVariants[c->forced_variant].steps;
+        steps = kVariants[c->forced_variant].family();
     return steps;
 }
 
@@ -184,6 +184,8 @@ int run_wave(eig_ctx* c, const std::vector<SolveSpec>& solves,
 
 size_t tiles_of(const eig_grid& g, const StencilVariant& v) {
     if (v.resident) return 1;  // one workgroup per solve
+    if (v.stream)              // at most: the shortest chunks
+        return stream_strips(g.nx, 1).size() * stream_chunks(g.nz, kStreamRowsMin);
     return (size_t)((g.nx + v.cols - 1) / v.cols) * ((g.nz - 1 + v.rows - 1) / v.rows);
 }
 
@@ -202,7 +204,7 @@ void stencil_candidates(const eig_ctx* c, int kind, bool one_step, std::vector<i
     // buffers) or one
     const int steps = family_steps_of(c, kind, one_step);
     for (int v = 1; v < kNumVariants; ++v)
-        if (kVariants[v].medium_kind == kind && kVariants[v].steps == steps &&
+        if (kVariants[v].medium_kind == kind && kVariants[v].family() == steps &&
             !kVariants[v].resident && !kVariants[v].forced_only)
             out.push_back(v);
     if (out.empty()) out.push_back(kind == EIG_MEDIUM_NODAL ? 6 : 0);
@@ -235,7 +237,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
     std::sort(rec_used.begin(), rec_used.end());
     rec_used.erase(std::unique(rec_used.begin(), rec_used.end()), rec_used.end());
     std::map<int, size_t> med_off;
-    for (int m : med_used) med_off[m] = cv.take(medium_bytes(media[m]));
+    for (int m : med_used) med_off[m] = cv.take(medium_bytes(media[m])) + medium_table(media[m].kind);
     // stencil variants this wave may use, per solve class (medium kind,
     // absorbing edges, dual solve): the last two need one step per launch
     std::vector<int> cands[2][2];
@@ -249,6 +251,14 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
     std::vector<char> res(n);
     for (int i = 0; i < n; ++i)
         res[i] = resident_ok(c, grids[solves[i].grid], media[solves[i].medium].kind);
+    // few tiles: the kernel with the tile in LDS instead of the streaming one
+    if (c->forced_variant < 0 && kVariants[cands[EIG_MEDIUM_LAYERED][0][0]].stream) {
+        std::vector<StreamLoad> l;
+        for (int i = 0; i < n; ++i)
+            if (!res[i] && !one_step(i) && media[solves[i].medium].kind == EIG_MEDIUM_LAYERED)
+                l.push_back({grids[solves[i].grid].nx, grids[solves[i].grid].nz, 1});
+        if (lds_launch(l)) cands[EIG_MEDIUM_LAYERED][0].assign(1, kLdsVariant);
+    }
     auto cand_of = [&](int i) -> const std::vector<int>& {
         if (res[i]) return res_cand[media[solves[i].medium].kind];
         return cands[media[solves[i].medium].kind][one_step(i) ? 1 : 0];
@@ -333,6 +343,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
         int kind, bc, cls;
         int first, last;               // solve range in launch order
         size_t lds = 0;                // resident groups: dynamic LDS bytes
+        StreamCut cut;                 // stream variants
         std::vector<int> cand;         // candidate variants
         std::vector<std::vector<int2>> tiles;                     // per candidate
         std::vector<std::vector<std::pair<int, int>>> steps_tiles;  // per candidate
@@ -340,6 +351,14 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
         std::vector<std::vector<std::pair<int, int>>> steps_htiles;
     };
     std::vector<Group> groups;
+    std::map<int, std::vector<StreamLoad>> loads;  // per class: what a launch streams
+    for (int i = 0; i < n; ++i) {
+        if (!kVariants[cand_of(i)[0]].stream) continue;
+        const eig_grid& g = grids[solves[i].grid];
+        auto& l = loads[class_of(i)];
+        if (!l.empty() && l.back().nx == g.nx && l.back().nz == g.nz) l.back().solves += 1;
+        else l.push_back({g.nx, g.nz, 1});
+    }
     for (int oi = 0; oi < n; ++oi) {
         const int i = ord[oi];
         const SolveSpec& sp = solves[i];
@@ -399,6 +418,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
             gr.cls = class_of(i);
             gr.first = oi;
             gr.cand = cand_of(i);
+            if (kVariants[gr.cand[0]].stream) gr.cut = stream_cut(loads[gr.cls]);
             gr.tiles.resize(gr.cand.size());
             gr.steps_tiles.resize(gr.cand.size());
             gr.htiles.resize(gr.cand.size());
@@ -413,6 +433,14 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                 gr.tiles[v].push_back(make_int2(oi, g.bc == EIG_BC_ABSORBING ? 1 : 0));
                 gr.steps_tiles[v].push_back({g.nsteps, (int)gr.tiles[v].size()});
                 gr.lds = std::max(gr.lds, resident_lds_bytes(mk.kind, g.nx, g.nz));
+                continue;
+            }
+            if (sv.stream) {
+                const auto strips = stream_strips(g.nx, gr.cut.narrow);
+                for (int ch = 0; ch < stream_chunks(g.nz, gr.cut.rows); ++ch)
+                    for (const auto& st : strips)
+                        gr.tiles[v].push_back(stream_tile(oi, st, ch));
+                gr.steps_tiles[v].push_back({g.nsteps, (int)gr.tiles[v].size()});
                 continue;
             }
             const int nstrip = (g.nx + sv.cols - 1) / sv.cols;
@@ -618,12 +646,12 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                                     g.lds, ls);
                 else if (!replay)
                     launch_stencil(ddesc, (const int2*)(bd + o_tiles[gi][vi]), ntile, step,
-                                   g.cand[vi], ls);
+                                   g.cand[vi], g.cut.rows, ls);
                 if (slot >= 0) HIP_TRY(hipEventRecord(tn.ev[2 * slot + 1], s));
                 if (g.bc == EIG_BC_ABSORBING && !replay && !resident &&
                     !(kVariants[g.cand[vi]].edges && c->fused_edges))
                     launch_ce_edges(ddesc + g.first, nrun, step, ls);
-                c->launches += 1;
+                c->launches += launch_units(kVariants[g.cand[vi]], step, stv.front().first);
                 c->updates += upd;
                 c->bytes += upd * (g.kind == EIG_MEDIUM_NODAL ? 36.0 : 24.0);
             }

@@ -1,6 +1,7 @@
 // Depth-only media, K leapfrog steps per launch with the tile kept in LDS
-// (variant 23: 58 x 58 tiles, K = 4; the temporal_blocking 4 family, the
-// default for rigid edges).
+// (variant 26: 58 x 58 tiles, K = 4; the temporal_blocking 4 family with rigid
+// edges runs it where a launch has few tiles, lds_launch, and the streaming
+// kernel elsewhere).
 //
 // A workgroup of 512 threads owns a TW x TH tile of one solve (two share a
 // CU).  It loads u^{m-1} and u^m on the tile and a K-node halo around it
@@ -23,7 +24,7 @@
 // LDS store (blk_load), so a workgroup waits for memory once; loading row by
 // row, a wave waited for each row's loads in turn, and the kernel ran no
 // faster than the two-step one (3.3e11 updates/s on the 512^2 Monte Carlo
-// query, against 4.4-4.5e11 now).
+// query, against 4.4-4.9e11 now).
 //
 // Work split: threads are packed over (band, column) pairs of the first
 // step's region, fixed for a tile; at step j a thread clips its column and

@@ -187,6 +187,16 @@ inline bool deviation_in_window(double coord, double step, double h) {
     return std::abs(a - b) <= kSrcW - 6;
 }
 
+// What launch number `step` of a solve group counts as in the launch
+// statistics: four-step launches where the streaming kernels run (each takes
+// the place of the four-step launches of its steps; nmax: the group's longest
+// solve), one otherwise.
+inline int64_t launch_units(const StencilVariant& v, int64_t step, int64_t nmax) {
+    if (!v.stream) return 1;
+    auto four = [&](int64_t launches) { return (std::min(launches * v.steps, nmax) + 3) / 4; };
+    return four(step + 1) - four(step);
+}
+
 inline int pitch_of(int nx) { return (nx + kPitchAlign - 1) / kPitchAlign * kPitchAlign; }
 
 struct SolveSpec {
@@ -239,10 +249,13 @@ inline size_t solve_bytes(const eig_grid& g) {
            align_up((size_t)std::max(g.nsteps, 1) * sizeof(float)) + 4 * kAlign;
 }
 
+// Offset of a medium's table in its medium_bytes (aligned as they are).
+inline size_t medium_table(int kind) { return kind == EIG_MEDIUM_NODAL ? 0 : kCoefPad; }
+
 inline size_t medium_bytes(const MediumKey& k) {
     if (k.kind == EIG_MEDIUM_NODAL)
         return align_up((size_t)3 * k.nz * pitch_of(k.nx) * sizeof(float)) + kAlign;
-    return align_up((size_t)k.nz * kCoefStride * sizeof(float)) + kAlign;
+    return align_up((size_t)k.nz * kCoefStride * sizeof(float)) + 2 * kCoefPad + kAlign;
 }
 
 

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "../../include/eigseis.h"
 
@@ -16,6 +17,10 @@ constexpr int kWavesPerBlock = 4;
 constexpr int kPitchAlign = 128; // row pitch (nodes) is a multiple of the widest tile
 constexpr int kSrcW = 7;         // source window: union of two 6x6 stencils
 constexpr int kCoefStride = 16;  // floats per row of a layered coefficient table
+// Readable bytes kept before and after a layered coefficient table: the
+// streaming kernels read the rows of levels that have not reached the grid's
+// first row yet, or have left its last, and drop what they form with them.
+constexpr size_t kCoefPad = 16 * kCoefStride * sizeof(float);
 
 // Coefficient slots of a layered table row (all pre-multiplied by
 // dt^2 / (rho_k h^2) except kFco = dt^2 / rho_k for the body force).
@@ -67,6 +72,9 @@ struct SolveDesc {
     // free row k, u^{m+1} and u^{m+2} at columns b-1 and b: [nb][nz][4]
     float2* side;
 };
+
+// Leapfrog steps per launch of the streaming kernels (even).
+constexpr int kStreamSteps = 8;
 
 // One forcing table to build (FP64 arithmetic, FP32 result).
 struct SourceJob {
@@ -148,6 +156,9 @@ struct StencilVariant {
     int edges;  // 1: runs edge tiles (absorbing edges in the same launch)
     int resident;  // 1: one workgroup per solve, fields in LDS, all steps in one launch
     int forced_only;  // 1: runs only when forced (not a tuning candidate)
+    int stream;       // 1: streams strips of rows through registers (stream.hip)
+    // the temporal_blocking value that selects it
+    int family() const { return steps >= 4 ? 4 : steps; }
 };
 // Tile entries (solve, kEdgeStrip << 16 | part) of a variant with `edges`:
 // absorbing edge nodes part * kEdgeTileNodes .. +kEdgeTileNodes of a solve.
@@ -156,18 +167,74 @@ constexpr int kEdgeTileNodes = 128;
 inline int edge_tiles_of(int nx, int nz) {
     return (2 * nz + nx - 2 + kEdgeTileNodes - 1) / kEdgeTileNodes;
 }
-constexpr int kNumVariants = 26;
+constexpr int kNumVariants = 27;
 extern const StencilVariant kVariants[kNumVariants];
 // tiles: (solve index, strip << 16 | chunk) per wavefront
+// (rows: rows per tile of the stream variants)
 void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
-                    int variant, hipStream_t s);
+                    int variant, int rows, hipStream_t s);
 // Tiled depth-only variants (0..5, 7..16) of launch_stencil.
 void launch_layered_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
                             int variant, hipStream_t s);
-// Variants 23 (depth-only) and 24, 25 (nodal) of launch_stencil: K steps
+// Variants 26 (depth-only) and 24, 25 (nodal) of launch_stencil: K steps
 // per launch with the tile in LDS, one workgroup per tile.
 void launch_blocked_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
                             int variant, hipStream_t s);
+// Tiles of the streaming kernels: one wave per (strip, chunk of rows) of a
+// solve.  A strip spans 128 columns, two per lane, or 64 (narrow), one per
+// lane, from x0 (even) on; the outer kStreamSteps columns of a side that is
+// not the grid's own edge only feed the others.  Tile entry: (solve,
+// x0 / 2 << 17 | narrow << 16 | chunk).
+struct StreamStrip {
+    int x0, narrow;
+};
+// How a launch is cut: rows per chunk, and whether every strip is narrow
+// (else only a last one that 64 columns finish).
+struct StreamCut {
+    int rows = 0, narrow = 0;
+    double us = 0.0;  // estimated launch time
+};
+inline std::vector<StreamStrip> stream_strips(int nx, int all_narrow) {
+    constexpr int K = kStreamSteps;
+    std::vector<StreamStrip> v;
+    for (int x0 = 0;;) {
+        const int narrow = all_narrow || x0 + 64 >= nx, w = narrow ? 64 : 128;
+        v.push_back({x0, narrow});
+        if (x0 + w >= nx) return v;
+        x0 += w - 2 * K;
+    }
+}
+inline int stream_chunks(int nz, int rows) { return (nz - 1 + rows - 1) / rows; }
+inline int2 stream_tile(int solve, StreamStrip st, int chunk) {
+    return make_int2(solve, (int)((unsigned)(st.x0 / 2) << 17 | (unsigned)st.narrow << 16 |
+                                  (unsigned)chunk));
+}
+constexpr int kStreamRowsMin = 8;
+// Depth-only launches of few tiles take four steps with the tile in LDS
+// (variant 26) instead: its 8 waves share a 58 x 58 tile's rows, while a
+// streaming wave takes its rows one after the other however few waves there
+// are.  Both estimates in us per eight steps (the LDS kernel's two launches;
+// the streaming one's start and its rows on the window and the surface, 19 us).
+// Measured, LDS against streaming: 1 solve of 512^2 (81 tiles) 26 / 36, 30 of
+// 200 x 150 (360) 36 / 48, 60 of 300 x 90 (720) 60 / 63, 60 of four uneven
+// grids (915) 69 / 80, 15 of 512^2 (1215) 84 / 84, 120 of 128^2 (1080) 66 / 63,
+// 60 of 384^2 (2940) 178 / 134, 105 of 256^2 (2625) 144 / 119.
+constexpr int kLdsVariant = 26;
+inline double lds_us(int64_t tiles) { return 16.0 + 26.0 * std::max(0.4, (double)tiles / 512.0); }
+inline int64_t lds_tiles(int nx, int nz) {
+    return (int64_t)((nx + 57) / 58) * ((nz - 1 + 57) / 58);
+}
+// The cut with the shortest estimated launch for `solves` solves of each
+// (nx, nz) (variants.hip).
+struct StreamLoad {
+    int nx, nz;
+    int64_t solves;
+};
+StreamCut stream_cut(const std::vector<StreamLoad>& loads);
+// Whether a launch over these solves is one for the LDS kernel.
+bool lds_launch(const std::vector<StreamLoad>& loads);
+void launch_layered_stream(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
+                           int rows, hipStream_t s);
 // Nodal-media variants (6, 17..20) of launch_stencil.
 void launch_nodal_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
                           int variant, hipStream_t s);

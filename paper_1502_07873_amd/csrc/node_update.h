@@ -84,26 +84,49 @@ __device__ __forceinline__ LayerCoef load_coef(const float* coef, int k) {
     return r;
 }
 
-// u^{m+1} at one node of a depth-only medium.  Every stencil variant calls
-// this, so all of them produce bitwise-identical fields.
+// Acceleration terms at one node of a depth-only medium (rm, rc, rn: rows k-1,
+// k, k+1), and u^{m+1} from them.  Every stencil variant goes through these
+// with the fused products spelled out (contraction off), so all of them
+// produce bitwise-identical fields whatever the code around the call.
+// TOP: the row may be the traction-free one, whose mixed terms take their own
+// row's x-differences (kCm0*, zero on every other row).
+template <bool TOP = true>
+__device__ __forceinline__ float2 layered_accel(const LayerCoef& c, const NodeRow& rm,
+                                                const NodeRow& rc, const NodeRow& rn) {
+#pragma clang fp contract(off)
+    const float xu = __builtin_fmaf(-2.f, rc.u, rc.sxu), xv = __builtin_fmaf(-2.f, rc.v, rc.sxv);
+    float au = __builtin_fmaf(c.c[kCxxU], xu, c.c[kCzpU] * (rn.u - rc.u));
+    float av = __builtin_fmaf(c.c[kCxxV], xv, c.c[kCzpV] * (rn.v - rc.v));
+    au = __builtin_fmaf(-(rc.u - rm.u), c.c[kCzmU], au);
+    av = __builtin_fmaf(-(rc.v - rm.v), c.c[kCzmV], av);
+    au = __builtin_fmaf(c.c[kCmpU], rn.dxv, au);
+    av = __builtin_fmaf(c.c[kCmpV], rn.dxu, av);
+    au = __builtin_fmaf(-rm.dxv, c.c[kCmmU], au);
+    av = __builtin_fmaf(-rm.dxu, c.c[kCmmV], av);
+    if constexpr (TOP) {
+        au = __builtin_fmaf(c.c[kCm0U], rc.dxv, au);
+        av = __builtin_fmaf(c.c[kCm0V], rc.dxu, av);
+    }
+    return make_float2(au, av);
+}
+
+__device__ __forceinline__ float2 layered_new(float2 a, float u, float v, float upu, float upv) {
+    float2 nw;
+    nw.x = u + ((u - upu) + a.x);
+    nw.y = v + ((v - upv) + a.y);
+    return nw;
+}
+
 __device__ __forceinline__ float2 layered_update(const LayerCoef& c, const NodeRow& rm,
                                                  const NodeRow& rc, const NodeRow& rn,
                                                  float upu, float upv, bool src, float fsv,
                                                  float wu, float wv) {
-    float au = c.c[kCxxU] * (rc.sxu - 2.f * rc.u) + c.c[kCzpU] * (rn.u - rc.u)
-             - c.c[kCzmU] * (rc.u - rm.u) + c.c[kCmpU] * rn.dxv
-             - c.c[kCmmU] * rm.dxv + c.c[kCm0U] * rc.dxv;
-    float av = c.c[kCxxV] * (rc.sxv - 2.f * rc.v) + c.c[kCzpV] * (rn.v - rc.v)
-             - c.c[kCzmV] * (rc.v - rm.v) + c.c[kCmpV] * rn.dxu
-             - c.c[kCmmV] * rm.dxu + c.c[kCm0V] * rc.dxu;
+    float2 a = layered_accel(c, rm, rc, rn);
     if (src) {
-        au += fsv * wu;
-        av += fsv * wv;
+        a.x = __builtin_fmaf(fsv, wu, a.x);
+        a.y = __builtin_fmaf(fsv, wv, a.y);
     }
-    float2 nw;
-    nw.x = rc.u + ((rc.u - upu) + au);
-    nw.y = rc.v + ((rc.v - upv) + av);
-    return nw;
+    return layered_new(a, rc.u, rc.v, upu, upv);
 }
 
 // An opaque copy: the compiler may not fuse the product that made x into a

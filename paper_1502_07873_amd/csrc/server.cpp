@@ -106,6 +106,7 @@ struct SrvGroup {
     int64_t start = 0;       // launch index of step 0 in the descriptors on the device
     int64_t done = 0;        // launches this group has taken
     bool on = false;         // in the current tile map
+    int variant = 0;         // stencil variant its launches run
     int nsteps = 0;
     size_t o_sd = 0, o_given = 0, o_sig = 0, o_work = 0;
     std::vector<SolveDesc> desc;  // host copy of its descriptors (start rewritten)
@@ -159,11 +160,15 @@ struct eig_server {
     // that cache instead of HBM; 0: admit whatever memory and slots allow
     size_t cache_bytes = 0;
     size_t live = 0;
-    int spl_layered = 1, spl_nodal = 1;  // leapfrog steps per launch of each kind's variant
     std::deque<SrvQuery*> queue;
     std::map<int64_t, std::unique_ptr<SrvQuery>> queries;
     std::vector<SrvGroup> groups;
-    std::vector<std::pair<int, size_t>> kind_tiles;  // (variant, ntiles) per kind range
+    struct KindTiles {
+        int variant;
+        size_t ntiles;
+        int rows;            // stream variants: rows per tile
+    };
+    std::vector<KindTiles> kind_tiles;  // per variant's range
     std::vector<size_t> kind_tile_off;
     bool tiles_dirty = true;
     int64_t next_id = 1;
@@ -172,9 +177,17 @@ struct eig_server {
 
 namespace {
 
-int spl_of(const eig_server* v, int kind) {
-    return kind == EIG_MEDIUM_NODAL ? v->spl_nodal : v->spl_layered;
+// The variant a group of G samples of q runs, for its whole life: a small
+// group's launches are too few tiles for the streaming kernel.
+int variant_of(const eig_server* v, const SrvQuery& q, int G) {
+    if (q.medium.kind == EIG_MEDIUM_NODAL) return v->variant_nodal;
+    if (kVariants[v->variant_layered].stream && v->ctx->forced_variant < 0 &&
+        lds_launch({{q.grid.nx, q.grid.nz, 15 * (int64_t)G}}))
+        return kLdsVariant;
+    return v->variant_layered;
 }
+
+int spl_of(const SrvGroup& gr) { return kVariants[gr.variant].steps; }
 
 // Admits one sample group of queued query q if memory, slots and the cache
 // limit allow (*ok), else leaves everything as it was.
@@ -184,7 +197,7 @@ int srv_admit_group(eig_server* v, SrvQuery& q, hipStream_t s, bool* ok) {
     {
         int G = std::min(v->group_samples, q.nsample - q.next_sample);
         G = std::min<int>(G, (int)(v->nslot_cap / 15));
-        const int spl = spl_of(v, q.medium.kind);
+        const int spl = kVariants[variant_of(v, q, G)].family();
         const size_t sample_live = (size_t)15 * (spl >= 2 ? 4 : 2) * q.grid.nz *
                                    pitch_of(q.grid.nx) * sizeof(float2);
         // the cache limit applies to queries one of whose samples fits it;
@@ -229,6 +242,7 @@ int srv_admit_group(eig_server* v, SrvQuery& q, hipStream_t s, bool* ok) {
         gr.live = cached ? (size_t)G * sample_live : 0;
         gr.start = v->launch;
         gr.nsteps = q.grid.nsteps;
+        gr.variant = variant_of(v, q, G);
         const bool four = spl >= 2;
         // carve the group's region
         char* base = v->mem + off;
@@ -236,7 +250,7 @@ int srv_admit_group(eig_server* v, SrvQuery& q, hipStream_t s, bool* ok) {
         const int nrec = (int)q.rec.size();
         MediumKey mk{q.medium.kind, q.medium.rho, q.medium.lam, q.medium.mu, g.nx, g.nz, g.h, g.dt};
         Carve cv;
-        const size_t o_coef = cv.take(medium_bytes(mk));
+        const size_t o_coef = cv.take(medium_bytes(mk)) + medium_table(mk.kind);
         const size_t o_map = cv.take((size_t)pitch_of(g.nx) * sizeof(int32_t));
         const size_t field = (size_t)g.nz * pitch_of(g.nx) * sizeof(float2);
         const size_t fields_begin = align_up(cv.off);
@@ -374,7 +388,7 @@ int srv_admit_group(eig_server* v, SrvQuery& q, hipStream_t s, bool* ok) {
 }
 
 double query_work_left(const eig_server* v, const SrvQuery& q);
-int64_t group_launches(const eig_server* v, const SrvGroup& gr);
+int64_t group_launches(const SrvGroup& gr);
 
 // Admission in the scheduler's order: queued queries by remaining work
 // (shortest first, then arrival), each taking as many groups as fit; a query
@@ -434,15 +448,15 @@ int srv_finish_query(eig_server* v, SrvQuery& q, hipStream_t s) {
 }
 
 // launches a group needs in total
-int64_t group_launches(const eig_server* v, const SrvGroup& gr) {
-    const int spl = spl_of(v, gr.q->medium.kind);
+int64_t group_launches(const SrvGroup& gr) {
+    const int spl = spl_of(gr);
     return (gr.nsteps + spl - 1) / spl;
 }
 
 int srv_retire(eig_server* v, hipStream_t s) {
     std::vector<SrvGroup> keep;
     for (auto& gr : v->groups) {
-        if (gr.done < group_launches(v, gr)) {
+        if (gr.done < group_launches(gr)) {
             keep.push_back(std::move(gr));
             continue;
         }
@@ -476,7 +490,7 @@ double query_work_left(const eig_server* v, const SrvQuery& q) {
     double w = 15.0 * (q.nsample - q.next_sample) * pts * q.grid.nsteps;
     for (const auto& gr : v->groups) {
         if (gr.q != &q) continue;
-        const int spl = spl_of(v, q.medium.kind);
+        const int spl = spl_of(gr);
         w += (double)gr.nslot * pts * std::max<int64_t>(0, gr.nsteps - spl * gr.done);
     }
     return w;
@@ -536,13 +550,33 @@ int srv_rebuild_tiles(eig_server* v, hipStream_t s) {
     std::vector<int2> all;
     v->kind_tiles.clear();
     v->kind_tile_off.clear();
-    for (int kind : {EIG_MEDIUM_LAYERED, EIG_MEDIUM_NODAL}) {
-        const int var = kind == EIG_MEDIUM_NODAL ? v->variant_nodal : v->variant_layered;
+    std::vector<int> vars;
+    for (const auto& gr : v->groups)
+        if (gr.on && std::find(vars.begin(), vars.end(), gr.variant) == vars.end())
+            vars.push_back(gr.variant);
+    for (int var : vars) {
         const StencilVariant& sv = kVariants[var];
+        const int kind = sv.medium_kind;
         const size_t begin = all.size();
+        StreamCut cut;
+        if (sv.stream) {
+            std::vector<StreamLoad> loads;
+            for (const auto& gr : v->groups)
+                if (gr.variant == var && gr.on)
+                    loads.push_back({gr.q->grid.nx, gr.q->grid.nz, (int64_t)gr.nslot});
+            cut = stream_cut(loads);
+        }
         for (const auto& gr : v->groups) {
-            if (gr.q->medium.kind != kind || !gr.on) continue;
+            if (gr.variant != var || !gr.on) continue;
             const eig_grid& g = gr.q->grid;
+            if (sv.stream && kind == EIG_MEDIUM_LAYERED) {
+                const auto strips = stream_strips(g.nx, cut.narrow);
+                for (size_t k = 0; k < gr.nslot; ++k)
+                    for (int ch = 0; ch < stream_chunks(g.nz, cut.rows); ++ch)
+                        for (const auto& st : strips)
+                            all.push_back(stream_tile((int)(gr.slot0 + k), st, ch));
+                continue;
+            }
             const int nstrip = (g.nx + sv.cols - 1) / sv.cols;
             const int nchunk = (g.nz - 1 + sv.rows - 1) / sv.rows;
             // a group's solves share one medium: on nodal media, sets of
@@ -558,7 +592,7 @@ int srv_rebuild_tiles(eig_server* v, hipStream_t s) {
                             all.push_back(make_int2((int)(gr.slot0 + k), (st << 16) | ch));
             }
         }
-        v->kind_tiles.push_back({var, all.size() - begin});
+        v->kind_tiles.push_back({var, all.size() - begin, cut.rows});
         v->kind_tile_off.push_back(begin);
     }
     if (all.size() > v->tile_cap) {
@@ -607,8 +641,6 @@ int eig_server_create(eig_ctx* c, size_t budget, int32_t group_samples, eig_serv
         v->variant_nodal = fv;
     else if (c->temporal_blocking == 4)
         v->variant_nodal = 24;
-    v->spl_layered = kVariants[v->variant_layered].steps;
-    v->spl_nodal = kVariants[v->variant_nodal].steps;
     v->nslot_cap = 1 << 17;
     if (hipMalloc((void**)&v->mem, budget) != hipSuccess) {
         (void)hipGetLastError();
@@ -731,7 +763,7 @@ int eig_server_step(eig_server* v, int32_t max_launches, void* stream, int32_t* 
         if ((rc = srv_rebuild_tiles(v, s))) return rc;
         int64_t seg = max_launches - done;
         for (const auto& gr : v->groups)
-            if (gr.on) seg = std::min(seg, group_launches(v, gr) - gr.done);
+            if (gr.on) seg = std::min(seg, group_launches(gr) - gr.done);
         // queries none of whose admitted groups run in this segment
         std::vector<SrvQuery*> paused;
         for (const auto& gr : v->groups) {
@@ -744,7 +776,7 @@ int eig_server_step(eig_server* v, int32_t max_launches, void* stream, int32_t* 
             double upd = 0.0;
             for (auto& gr : v->groups) {
                 if (!gr.on) continue;
-                const int spl = spl_of(v, gr.q->medium.kind);
+                const int spl = spl_of(gr);
                 const int64_t left = gr.nsteps - spl * gr.done;
                 upd += (double)gr.q->grid.nx * gr.q->grid.nz * gr.nslot *
                        (double)std::min<int64_t>(spl, left);
@@ -754,11 +786,11 @@ int eig_server_step(eig_server* v, int32_t max_launches, void* stream, int32_t* 
             v->work_done += upd;
             for (SrvQuery* q : paused) q->waited += upd;
             for (size_t kk = 0; kk < v->kind_tiles.size(); ++kk) {
-                const size_t nt = v->kind_tiles[kk].second;
-                if (nt == 0) continue;
-                launch_stencil(v->descs, v->tiles + v->kind_tile_off[kk], (int)nt,
-                               (int)v->launch, v->kind_tiles[kk].first, s);
-                c->launches += 1;
+                const auto& kt = v->kind_tiles[kk];
+                if (kt.ntiles == 0) continue;
+                launch_stencil(v->descs, v->tiles + v->kind_tile_off[kk], (int)kt.ntiles,
+                               (int)v->launch, kt.variant, kt.rows, s);
+                c->launches += kVariants[kt.variant].stream ? kVariants[kt.variant].steps / 4 : 1;
             }
             ++v->launch;
         }

@@ -1,7 +1,11 @@
 // The stencil variants the host may run and their launcher.  All give
 // bitwise-identical fields; they differ in tile shape, steps per launch and
 // speed (tiled depth-only kernels: stencil.hip; nodal: nodal.hip; tile in LDS
-// over several steps, both media: blocked.hip; whole solves in LDS: resident.hip).
+// over several steps, both media: blocked.hip; strips streamed through
+// registers over several steps: stream.hip; whole solves in LDS: resident.hip).
+#include <map>
+#include <utility>
+
 #include "internal.h"
 
 namespace eig {
@@ -30,20 +34,73 @@ const StencilVariant kVariants[kNumVariants] = {
     {128, 32, EIG_MEDIUM_NODAL, 2},    // 20: nodal media, two steps per launch
     {0, 0, EIG_MEDIUM_LAYERED, 1, 1, 1},  // 21: resident in LDS, every step in one launch
     {0, 0, EIG_MEDIUM_NODAL, 1, 1, 1},    // 22: resident in LDS, every step in one launch
-    {58, 58, EIG_MEDIUM_LAYERED, 4},   // 23: four steps per launch, tile in LDS
+    {0, 0, EIG_MEDIUM_LAYERED, kStreamSteps, 0, 0, 0, 1},  // 23: strips streamed through registers
     {58, 34, EIG_MEDIUM_NODAL, 4},     // 24: nodal, four steps, tile and medium in LDS
     {64, 24, EIG_MEDIUM_NODAL, 4, 0, 0, 1},  // 25: the same, operands read per node (forced only)
+    {58, 58, EIG_MEDIUM_LAYERED, 4, 0, 0, 1},  // 26: four steps, tile in LDS (small launches)
 };
 
 void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
-                    int variant, hipStream_t s) {
+                    int variant, int rows, hipStream_t s) {
     if (ntiles <= 0) return;
-    if (kVariants[variant].steps == 4)
+    if (kVariants[variant].stream)
+        launch_layered_stream(descs, tiles, ntiles, step, rows, s);
+    else if (kVariants[variant].steps == 4)
         launch_blocked_stencil(descs, tiles, ntiles, step, variant, s);
     else if (kVariants[variant].medium_kind == EIG_MEDIUM_NODAL)
         launch_nodal_stencil(descs, tiles, ntiles, step, variant, s);
     else
         launch_layered_stencil(descs, tiles, ntiles, step, variant, s);
+}
+
+// A launch's time in the units of one wide row (K levels of 128 columns) on a
+// SIMD of its own, 1.0 us: a wave takes rows + 2 K of them, a narrow row 0.65,
+// and two waves of a SIMD slow each other down 1.65 times (measured per launch
+// over 15 to 960 solves of 128 to 512 columns).  Up to the chip's 2048 waves
+// (two per SIMD) a launch takes as long as one wave; a few more wait for a
+// whole further one; from 1.25 rounds on the waves' ends are spread enough for
+// the work to count, and half a wave for the end.
+StreamCut stream_cut(const std::vector<StreamLoad>& all) {
+    constexpr int K = kStreamSteps;
+    constexpr double kPair = 1.65, kSlots = 2048.0;
+    std::map<std::pair<int, int>, int64_t> grids;
+    for (const auto& l : all) grids[{l.nx, l.nz}] += l.solves;
+    std::vector<StreamLoad> loads;
+    for (const auto& g : grids) loads.push_back({g.first.first, g.first.second, g.second});
+    int nzmax = 2;
+    for (const auto& l : loads) nzmax = std::max(nzmax, l.nz);
+    StreamCut best;
+    double best_t = 1e300;
+    for (int narrow = 0; narrow < 2; ++narrow)
+        for (int n = 1; n <= std::max(1, (nzmax - 1) / kStreamRowsMin); n += 1 + n / 16) {
+            const int rows = stream_chunks(nzmax, n);  // ceil((nz - 1) / n)
+            double waves = 0.0, work = 0.0, longest = 0.0;
+            for (const auto& l : loads)
+                for (const auto& st : stream_strips(l.nx, narrow)) {
+                    const int c = stream_chunks(l.nz, rows);
+                    const double per = st.narrow ? 0.65 : 1.0;
+                    waves += (double)l.solves * c;
+                    work += (double)l.solves * per * (l.nz - 1 + c * 2.0 * K);
+                    longest = std::max(longest, per * (std::min(rows, l.nz - 1) + 2.0 * K));
+                }
+            const double rounds = waves / kSlots;
+            const double t = rounds <= 0.5    ? longest
+                             : rounds <= 1.0  ? kPair * longest
+                             : rounds <= 1.25 ? (kPair + 1.0) * longest
+                                              : kPair * work / kSlots + 0.5 * longest;
+            if (t < best_t) {
+                best_t = t;
+                best = StreamCut{rows, narrow, t + 19.0};
+            }
+        }
+    return best;
+}
+
+bool lds_launch(const std::vector<StreamLoad>& loads) {
+    int64_t tiles = 0;
+    for (const auto& l : loads) tiles += l.solves * lds_tiles(l.nx, l.nz);
+    // past 16 rounds of tiles the streaming kernel's rate is twice the other's
+    return tiles < 16 * 512 && lds_us(tiles) < stream_cut(loads).us;
 }
 
 }  // namespace eig
