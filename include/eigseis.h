@@ -219,9 +219,9 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
 int eig_ctx_set_option(eig_ctx* ctx, const char* name, int64_t value);
 /* Reads an option back; "last_variant" gives the stencil variant of the most
  * recent launch.  "temporal_blocking": leapfrog steps per launch for media
- * with rigid edges, 4 (default: four or more; depth-only variants 23, eight
- * steps streamed through registers, and 26 for small launches, four with the
- * tile and its halo in LDS; nodal variants 24 and 25), 2 (1 also selects 2), 3
+ * with rigid edges, 4 (default: four or more; variants 23 and, nodal media, 24:
+ * eight and six steps streamed through registers; for small launches 26 and
+ * 27: four with the tile and its halo in LDS, 25 a forced-only form of 27), 2 (1 also selects 2), 3
  * (depth-only media; nodal media then take two), or 0 for one step; two to
  * four steps per launch keep four field buffers per solve.  Serving engines
  * created while it is 4 run those variants for both media; otherwise two for depth-only media and one for nodal media. */

@@ -185,7 +185,7 @@ int run_wave(eig_ctx* c, const std::vector<SolveSpec>& solves,
 size_t tiles_of(const eig_grid& g, const StencilVariant& v) {
     if (v.resident) return 1;  // one workgroup per solve
     if (v.stream)              // at most: the shortest chunks
-        return stream_strips(g.nx, 1).size() * stream_chunks(g.nz, kStreamRowsMin);
+        return stream_strips(g.nx, 1, v.steps).size() * stream_chunks(g.nz, kStreamRowsMin);
     return (size_t)((g.nx + v.cols - 1) / v.cols) * ((g.nz - 1 + v.rows - 1) / v.rows);
 }
 
@@ -252,12 +252,14 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
     for (int i = 0; i < n; ++i)
         res[i] = resident_ok(c, grids[solves[i].grid], media[solves[i].medium].kind);
     // few tiles: the kernel with the tile in LDS instead of the streaming one
-    if (c->forced_variant < 0 && kVariants[cands[EIG_MEDIUM_LAYERED][0][0]].stream) {
+    for (int kind = 0; kind < 2 && c->forced_variant < 0; ++kind) {
+        std::vector<int>& cd = cands[kind][0];
+        if (!kVariants[cd[0]].stream) continue;
         std::vector<StreamLoad> l;
         for (int i = 0; i < n; ++i)
-            if (!res[i] && !one_step(i) && media[solves[i].medium].kind == EIG_MEDIUM_LAYERED)
+            if (!res[i] && !one_step(i) && media[solves[i].medium].kind == kind)
                 l.push_back({grids[solves[i].grid].nx, grids[solves[i].grid].nz, 1});
-        if (lds_launch(l)) cands[EIG_MEDIUM_LAYERED][0].assign(1, kLdsVariant);
+        if (!l.empty()) cd.assign(1, small_launch_variant(cd[0], l));
     }
     auto cand_of = [&](int i) -> const std::vector<int>& {
         if (res[i]) return res_cand[media[solves[i].medium].kind];
@@ -418,7 +420,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
             gr.cls = class_of(i);
             gr.first = oi;
             gr.cand = cand_of(i);
-            if (kVariants[gr.cand[0]].stream) gr.cut = stream_cut(loads[gr.cls]);
+            if (kVariants[gr.cand[0]].stream) gr.cut = stream_cut(gr.cand[0], loads[gr.cls]);
             gr.tiles.resize(gr.cand.size());
             gr.steps_tiles.resize(gr.cand.size());
             gr.htiles.resize(gr.cand.size());
@@ -436,7 +438,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                 continue;
             }
             if (sv.stream) {
-                const auto strips = stream_strips(g.nx, gr.cut.narrow);
+                const auto strips = stream_strips(g.nx, gr.cut.narrow, sv.steps);
                 for (int ch = 0; ch < stream_chunks(g.nz, gr.cut.rows); ++ch)
                     for (const auto& st : strips)
                         gr.tiles[v].push_back(stream_tile(oi, st, ch));

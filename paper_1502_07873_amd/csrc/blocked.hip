@@ -1,6 +1,6 @@
 // Depth-only media, K leapfrog steps per launch with the tile kept in LDS
 // (variant 26: 58 x 58 tiles, K = 4; the temporal_blocking 4 family with rigid
-// edges runs it where a launch has few tiles, lds_launch, and the streaming
+// edges runs it where a launch has few tiles, small_launch_variant, and the streaming
 // kernel elsewhere).
 //
 // A workgroup of 512 threads owns a TW x TH tile of one solve (two share a
@@ -310,7 +310,7 @@ struct NodalRow3 {
 };
 
 // Step j of a tile whose region, medium and forcing are in LDS, each thread
-// streaming down its band of one column (variant 24).
+// streaming down its band of one column (variant 27).
 template <int K, int RW, class FLD, class CL>
 __device__ __forceinline__ void nodal_lds_stream(const BlkTile& tl, const BlkLane& ln, int rec,
                                                  int j, FLD fld, CL cl, const float* sw_lds,
@@ -410,14 +410,14 @@ __device__ __forceinline__ void nodal_lds_stream(const BlkTile& tl, const BlkLan
     }
 }
 
-// Nodal media, K steps per launch (variant 24: 58 x 34 tiles; the
+// Nodal media, K steps per launch (variant 27: 58 x 34 tiles; the
 // forced-only variant 25: 64 x 24; two 512-thread workgroups per CU).  Same
 // passes, buffer pairs, regions and receiver ownership as the depth-only
 // kernel above; LDS also holds lambda, mu and dt^2/(rho h^2) over the region
 // (28 B per region node with both field levels: 78 KB at 66 x 42, the
 // tallest region two workgroups per CU can hold: each wave's band gets 5
 // rows of the first step, 4 with 26-row tiles, which ran 8 % slower).  Variant
-// 24 (STREAM) gives each wave one band of the 64-column first region and
+// 27 (STREAM) gives each wave one band of the 64-column first region and
 // streams down its rows with u, v, lambda and mu of rows k-1, k, k+1 and
 // columns i-1, i, i+1 in registers; variant 25 gives thread t the nodes t,
 // t + NT, ... of a step's region in row-major order and reads every operand
@@ -535,7 +535,7 @@ stencil_nodal_lds(const SolveDesc* __restrict__ descs, const int2* __restrict__ 
 void launch_blocked_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
                             int variant, hipStream_t s) {
     switch (variant) {
-        case 24:
+        case 27:
             stencil_nodal_lds<58, 34, 4, 512, 2, true><<<ntiles, 512, 0, s>>>(descs, tiles,
                                                                               ntiles, pass);
             break;

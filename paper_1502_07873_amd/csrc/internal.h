@@ -74,7 +74,7 @@ struct SolveDesc {
 };
 
 // Leapfrog steps per launch of the streaming kernels (even).
-constexpr int kStreamSteps = 8;
+constexpr int kStreamSteps = 8, kNodalStreamSteps = 6;
 
 // One forcing table to build (FP64 arithmetic, FP32 result).
 struct SourceJob {
@@ -167,7 +167,7 @@ constexpr int kEdgeTileNodes = 128;
 inline int edge_tiles_of(int nx, int nz) {
     return (2 * nz + nx - 2 + kEdgeTileNodes - 1) / kEdgeTileNodes;
 }
-constexpr int kNumVariants = 27;
+constexpr int kNumVariants = 28;
 extern const StencilVariant kVariants[kNumVariants];
 // tiles: (solve index, strip << 16 | chunk) per wavefront
 // (rows: rows per tile of the stream variants)
@@ -182,8 +182,8 @@ void launch_blocked_stencil(const SolveDesc* descs, const int2* tiles, int ntile
                             int variant, hipStream_t s);
 // Tiles of the streaming kernels: one wave per (strip, chunk of rows) of a
 // solve.  A strip spans 128 columns, two per lane, or 64 (narrow), one per
-// lane, from x0 (even) on; the outer kStreamSteps columns of a side that is
-// not the grid's own edge only feed the others.  Tile entry: (solve,
+// lane, from x0 (even) on; the outer K columns of a side that is not the
+// grid's own edge only feed the others (K: the kernel's steps per launch).  Tile entry: (solve,
 // x0 / 2 << 17 | narrow << 16 | chunk).
 struct StreamStrip {
     int x0, narrow;
@@ -194,8 +194,7 @@ struct StreamCut {
     int rows = 0, narrow = 0;
     double us = 0.0;  // estimated launch time
 };
-inline std::vector<StreamStrip> stream_strips(int nx, int all_narrow) {
-    constexpr int K = kStreamSteps;
+inline std::vector<StreamStrip> stream_strips(int nx, int all_narrow, int K) {
     std::vector<StreamStrip> v;
     for (int x0 = 0;;) {
         const int narrow = all_narrow || x0 + 64 >= nx, w = narrow ? 64 : 128;
@@ -210,29 +209,18 @@ inline int2 stream_tile(int solve, StreamStrip st, int chunk) {
                                   (unsigned)chunk));
 }
 constexpr int kStreamRowsMin = 8;
-// Depth-only launches of few tiles take four steps with the tile in LDS
-// (variant 26) instead: its 8 waves share a 58 x 58 tile's rows, while a
-// streaming wave takes its rows one after the other however few waves there
-// are.  Both estimates in us per eight steps (the LDS kernel's two launches;
-// the streaming one's start and its rows on the window and the surface, 19 us).
-// Measured, LDS against streaming: 1 solve of 512^2 (81 tiles) 26 / 36, 30 of
-// 200 x 150 (360) 36 / 48, 60 of 300 x 90 (720) 60 / 63, 60 of four uneven
-// grids (915) 69 / 80, 15 of 512^2 (1215) 84 / 84, 120 of 128^2 (1080) 66 / 63,
-// 60 of 384^2 (2940) 178 / 134, 105 of 256^2 (2625) 144 / 119.
-constexpr int kLdsVariant = 26;
-inline double lds_us(int64_t tiles) { return 16.0 + 26.0 * std::max(0.4, (double)tiles / 512.0); }
-inline int64_t lds_tiles(int nx, int nz) {
-    return (int64_t)((nx + 57) / 58) * ((nz - 1 + 57) / 58);
-}
-// The cut with the shortest estimated launch for `solves` solves of each
-// (nx, nz) (variants.hip).
+// The cut with the shortest estimated launch of stream variant v for `solves`
+// solves of each (nx, nz) (variants.hip).
 struct StreamLoad {
     int nx, nz;
     int64_t solves;
 };
-StreamCut stream_cut(const std::vector<StreamLoad>& loads);
-// Whether a launch over these solves is one for the LDS kernel.
-bool lds_launch(const std::vector<StreamLoad>& loads);
+StreamCut stream_cut(int v, const std::vector<StreamLoad>& loads);
+// The variant that takes stream variant v's place for a launch over these
+// solves: v itself, or where they are few tiles the kernel with the tile in LDS.
+int small_launch_variant(int v, const std::vector<StreamLoad>& loads);
+void launch_nodal_stream(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
+                         int rows, hipStream_t s);
 void launch_layered_stream(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
                            int rows, hipStream_t s);
 // Nodal-media variants (6, 17..20) of launch_stencil.

@@ -180,11 +180,9 @@ namespace {
 // The variant a group of G samples of q runs, for its whole life: a small
 // group's launches are too few tiles for the streaming kernel.
 int variant_of(const eig_server* v, const SrvQuery& q, int G) {
-    if (q.medium.kind == EIG_MEDIUM_NODAL) return v->variant_nodal;
-    if (kVariants[v->variant_layered].stream && v->ctx->forced_variant < 0 &&
-        lds_launch({{q.grid.nx, q.grid.nz, 15 * (int64_t)G}}))
-        return kLdsVariant;
-    return v->variant_layered;
+    const int var = q.medium.kind == EIG_MEDIUM_NODAL ? v->variant_nodal : v->variant_layered;
+    if (!kVariants[var].stream || v->ctx->forced_variant >= 0) return var;
+    return small_launch_variant(var, {{q.grid.nx, q.grid.nz, 15 * (int64_t)G}});
 }
 
 int spl_of(const SrvGroup& gr) { return kVariants[gr.variant].steps; }
@@ -564,26 +562,27 @@ int srv_rebuild_tiles(eig_server* v, hipStream_t s) {
             for (const auto& gr : v->groups)
                 if (gr.variant == var && gr.on)
                     loads.push_back({gr.q->grid.nx, gr.q->grid.nz, (int64_t)gr.nslot});
-            cut = stream_cut(loads);
+            cut = stream_cut(var, loads);
         }
         for (const auto& gr : v->groups) {
             if (gr.variant != var || !gr.on) continue;
             const eig_grid& g = gr.q->grid;
-            if (sv.stream && kind == EIG_MEDIUM_LAYERED) {
-                const auto strips = stream_strips(g.nx, cut.narrow);
-                for (size_t k = 0; k < gr.nslot; ++k)
-                    for (int ch = 0; ch < stream_chunks(g.nz, cut.rows); ++ch)
-                        for (const auto& st : strips)
-                            all.push_back(stream_tile((int)(gr.slot0 + k), st, ch));
-                continue;
-            }
-            const int nstrip = (g.nx + sv.cols - 1) / sv.cols;
-            const int nchunk = (g.nz - 1 + sv.rows - 1) / sv.rows;
             // a group's solves share one medium: on nodal media, sets of
             // coef_interleave solves run position-major (coefficients read
             // from L2 once per set; the order changes no result)
             const size_t set = kind == EIG_MEDIUM_NODAL
                                    ? (size_t)std::max(v->ctx->coef_interleave, 1) : 1;
+            if (sv.stream) {
+                const auto strips = stream_strips(g.nx, cut.narrow, sv.steps);
+                for (size_t k0 = 0; k0 < gr.nslot; k0 += set)
+                    for (int ch = 0; ch < stream_chunks(g.nz, cut.rows); ++ch)
+                        for (const auto& st : strips)
+                            for (size_t k = k0; k < std::min(gr.nslot, k0 + set); ++k)
+                                all.push_back(stream_tile((int)(gr.slot0 + k), st, ch));
+                continue;
+            }
+            const int nstrip = (g.nx + sv.cols - 1) / sv.cols;
+            const int nchunk = (g.nz - 1 + sv.rows - 1) / sv.rows;
             for (size_t k0 = 0; k0 < gr.nslot; k0 += set) {
                 const size_t k1 = std::min(gr.nslot, k0 + set);
                 for (int ch = 0; ch < nchunk; ++ch)

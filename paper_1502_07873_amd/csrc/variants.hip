@@ -35,15 +35,18 @@ const StencilVariant kVariants[kNumVariants] = {
     {0, 0, EIG_MEDIUM_LAYERED, 1, 1, 1},  // 21: resident in LDS, every step in one launch
     {0, 0, EIG_MEDIUM_NODAL, 1, 1, 1},    // 22: resident in LDS, every step in one launch
     {0, 0, EIG_MEDIUM_LAYERED, kStreamSteps, 0, 0, 0, 1},  // 23: strips streamed through registers
-    {58, 34, EIG_MEDIUM_NODAL, 4},     // 24: nodal, four steps, tile and medium in LDS
-    {64, 24, EIG_MEDIUM_NODAL, 4, 0, 0, 1},  // 25: the same, operands read per node (forced only)
+    {0, 0, EIG_MEDIUM_NODAL, kNodalStreamSteps, 0, 0, 0, 1},  // 24: the same, nodal media
+    {64, 24, EIG_MEDIUM_NODAL, 4, 0, 0, 1},  // 25: as 27, operands read per node (forced only)
     {58, 58, EIG_MEDIUM_LAYERED, 4, 0, 0, 1},  // 26: four steps, tile in LDS (small launches)
+    {58, 34, EIG_MEDIUM_NODAL, 4, 0, 0, 1},  // 27: the same, nodal: tile and medium in LDS
 };
 
 void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
                     int variant, int rows, hipStream_t s) {
     if (ntiles <= 0) return;
-    if (kVariants[variant].stream)
+    if (kVariants[variant].stream && kVariants[variant].medium_kind == EIG_MEDIUM_NODAL)
+        launch_nodal_stream(descs, tiles, ntiles, step, rows, s);
+    else if (kVariants[variant].stream)
         launch_layered_stream(descs, tiles, ntiles, step, rows, s);
     else if (kVariants[variant].steps == 4)
         launch_blocked_stencil(descs, tiles, ntiles, step, variant, s);
@@ -54,14 +57,14 @@ void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int s
 }
 
 // A launch's time in the units of one wide row (K levels of 128 columns) on a
-// SIMD of its own, 1.0 us: a wave takes rows + 2 K of them, a narrow row 0.65,
+// SIMD of its own, 1.0 us (nodal media 1.44 us): a wave takes rows + 2 K of them, a narrow row 0.65,
 // and two waves of a SIMD slow each other down 1.65 times (measured per launch
 // over 15 to 960 solves of 128 to 512 columns).  Up to the chip's 2048 waves
 // (two per SIMD) a launch takes as long as one wave; a few more wait for a
 // whole further one; from 1.25 rounds on the waves' ends are spread enough for
 // the work to count, and half a wave for the end.
-StreamCut stream_cut(const std::vector<StreamLoad>& all) {
-    constexpr int K = kStreamSteps;
+StreamCut stream_cut(int v, const std::vector<StreamLoad>& all) {
+    const int K = kVariants[v].steps;
     constexpr double kPair = 1.65, kSlots = 2048.0;
     std::map<std::pair<int, int>, int64_t> grids;
     for (const auto& l : all) grids[{l.nx, l.nz}] += l.solves;
@@ -76,7 +79,7 @@ StreamCut stream_cut(const std::vector<StreamLoad>& all) {
             const int rows = stream_chunks(nzmax, n);  // ceil((nz - 1) / n)
             double waves = 0.0, work = 0.0, longest = 0.0;
             for (const auto& l : loads)
-                for (const auto& st : stream_strips(l.nx, narrow)) {
+                for (const auto& st : stream_strips(l.nx, narrow, K)) {
                     const int c = stream_chunks(l.nz, rows);
                     const double per = st.narrow ? 0.65 : 1.0;
                     waves += (double)l.solves * c;
@@ -90,17 +93,34 @@ StreamCut stream_cut(const std::vector<StreamLoad>& all) {
                                               : kPair * work / kSlots + 0.5 * longest;
             if (t < best_t) {
                 best_t = t;
-                best = StreamCut{rows, narrow, t + 19.0};
+                const bool nodal = kVariants[v].medium_kind == EIG_MEDIUM_NODAL;
+                best = StreamCut{rows, narrow, (t * (nodal ? 1.44 : 1.0) + 19.0) * 8.0 / K};
             }
         }
     return best;
 }
 
-bool lds_launch(const std::vector<StreamLoad>& loads) {
+// Launches of few tiles take four steps with the tile in LDS instead: its 8
+// waves share the tile's rows (58 x 58 nodes, nodal media 58 x 34), while a
+// streaming wave takes its rows one after the other however few waves there
+// are.  Both estimates in us per eight steps (the LDS kernels' two launches; the
+// streaming ones' rows, and 19 us per launch for their start and their rows on
+// the window and the surface).  Measured, LDS against streaming, depth-only: 1 solve of 512^2 (81 tiles) 26 / 36, 30 of 200 x 150
+// (360) 36 / 48, 60 of 300 x 90 (720) 60 / 63, 60 of four uneven grids (915)
+// 69 / 80, 15 of 512^2 (1215) 84 / 84, 120 of 128^2 (1080) 66 / 63, 60 of 384^2
+// (2940) 178 / 134, 105 of 256^2 (2625) 144 / 119; nodal: 1 of 512^2 (144) 24 /
+// 41, 30 of 200 x 150 (600) 50 / 58, 30 of 300 x 200 (1080) 76 / 82, 120 of
+// 128^2 (1440) 85 / 77, 90 of 300 x 200 (3240) 169 / 147.
+int small_launch_variant(int v, const std::vector<StreamLoad>& loads) {
+    const int lds = kVariants[v].medium_kind == EIG_MEDIUM_NODAL ? 27 : 26;
+    const int tw = kVariants[lds].cols, th = kVariants[lds].rows;
     int64_t tiles = 0;
-    for (const auto& l : loads) tiles += l.solves * lds_tiles(l.nx, l.nz);
+    for (const auto& l : loads)
+        tiles += l.solves * ((l.nx + tw - 1) / tw) * ((l.nz - 1 + th - 1) / th);
     // past 16 rounds of tiles the streaming kernel's rate is twice the other's
-    return tiles < 16 * 512 && lds_us(tiles) < stream_cut(loads).us;
+    if (tiles >= 16 * 512) return v;
+    const double us = 16.0 + 26.0 * std::max(0.4, (double)tiles / 512.0);
+    return us < stream_cut(v, loads).us ? lds : v;
 }
 
 }  // namespace eig

@@ -46,7 +46,8 @@ def _run(variant, grid, medium, th, rec):
 # it, two wide, wide and narrow; nz: one row per chunk up to several chunks.
 # `solves`: few (narrow strips, short chunks) or enough waves for wide strips
 # and long chunks (400: several rounds of the chip)
-@pytest.mark.parametrize("kind,variant,base", [("layered", 23, 0), ("layered", 26, 0)])
+@pytest.mark.parametrize("kind,variant,base", [("layered", 23, 0), ("layered", 26, 0),
+                                               ("nodal", 24, 6), ("nodal", 27, 6)])
 @pytest.mark.parametrize("nx,nz,solves", [(8, 8, 2), (64, 9, 3), (65, 17, 3), (121, 24, 3),
                                           (128, 25, 3), (129, 33, 2), (176, 40, 2), (177, 16, 2),
                                           (240, 18, 400), (129, 50, 400), (241, 10, 2)])
