@@ -94,7 +94,8 @@ typedef struct eig_ctx eig_ctx;
  * (one-sided at the ends of the edge, corners take their column's relation);
  * time is the centred difference of Section 3.3.1 with the node's own
  * same-component term taken at the mean of levels m+1 and m-1 (the fully
- * explicit form diverges).  Such grids always run one step per launch. */
+ * explicit form diverges).  Depth-only forward solves on
+ * such grids run several steps per launch by default, others one. */
 typedef struct {
     int32_t nx, nz;
     double h, dt;
@@ -212,7 +213,8 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
  *   "fused_edges"      1 (default): the two-nodes-per-lane one-step kernels
  *                      update absorbing edge nodes in extra wavefronts of
  *                      their own launch; 0: a separate edge kernel after each
- *                      launch.  Same results either way.
+ *                      launch (and one step per launch).  Same results either
+ *                      way.
  *   "max_wave_solves"  0 (default): no limit; n > 0: at most n solves per
  *                      launch (n = 1 is the plain one-solve-at-a-time path)
  * EIG_EINVAL for an unknown name or value. */
@@ -221,10 +223,12 @@ int eig_ctx_set_option(eig_ctx* ctx, const char* name, int64_t value);
  * recent launch.  "temporal_blocking": leapfrog steps per launch for media
  * with rigid edges, 4 (default: four or more; variants 23 and, nodal media, 24:
  * eight and six steps streamed through registers; for small launches 26 and
- * 27: four with the tile and its halo in LDS, 25 a forced-only form of 27), 2 (1 also selects 2), 3
+ * 27: four with the tile and its halo in LDS, 25 a forced-only form of 27;
+ * forward solves of depth-only media with absorbing edges 28: six), 2 (1 also selects 2), 3
  * (depth-only media; nodal media then take two), or 0 for one step; two to
  * four steps per launch keep four field buffers per solve.  Serving engines
- * created while it is 4 run those variants for both media; otherwise two for depth-only media and one for nodal media. */
+ * created while it is 4 run those variants for both media; otherwise two for
+ * depth-only media and one for nodal media. */
 int eig_ctx_get_option(const eig_ctx* ctx, const char* name, int64_t* value);
 
 /*

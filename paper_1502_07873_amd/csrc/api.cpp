@@ -68,14 +68,25 @@ int family_steps_of(const eig_ctx* c, int kind, bool one_step) {
     return std::min(c->temporal_blocking, 2);
 }
 
+// Whether a solve with absorbing edges that is not resident streams several
+// steps per launch (variant 28): depth-only media, forward solves, unless a
+// variant, fewer steps per launch or the separate edge kernel is asked for.
+bool absorbing_stream(const eig_ctx* c, const SolveSpec& sp, const eig_grid& g,
+                      const MediumKey& mk) {
+    return g.bc == EIG_BC_ABSORBING && sp.rforce == nullptr && mk.kind == EIG_MEDIUM_LAYERED &&
+           c->temporal_blocking == 4 && c->fused_edges &&
+           (c->forced_variant < 0 || c->forced_variant == kAbsorbingStream);
+}
+
 // Leapfrog steps per launch of a tiled solve (a forced variant's, else its
 // family's).
 int tiled_steps_of(const eig_ctx* c, const SolveSpec& sp, const eig_grid& g,
                    const MediumKey& mk) {
+    if (absorbing_stream(c, sp, g, mk)) return 4;
     const bool one_step = g.bc == EIG_BC_ABSORBING || sp.rforce != nullptr;
     int steps = family_steps_of(c, mk.kind, one_step);
     if (c->forced_variant >= 0 && kVariants[c->forced_variant].medium_kind == mk.kind &&
-        !kVariants[c->forced_variant].resident &&
+        !kVariants[c->forced_variant].resident && !kVariants[c->forced_variant].absorbing &&
         !(one_step && kVariants[c->forced_variant].steps != 1))
         steps = kVariants[c->forced_variant].family();
     return steps;
@@ -182,10 +193,13 @@ int run_wave(eig_ctx* c, const std::vector<SolveSpec>& solves,
     return EIG_OK;
 }
 
+// No solve class has more candidates (a family of its medium's variants).
+constexpr size_t kMapVariants = 8;
+
 size_t tiles_of(const eig_grid& g, const StencilVariant& v) {
     if (v.resident) return 1;  // one workgroup per solve
     if (v.stream)              // at most: the shortest chunks
-        return stream_strips(g.nx, 1, v.steps).size() * stream_chunks(g.nz, kStreamRowsMin);
+        return stream_strips(g.nx, 1, v.steps).size() * stream_chunks(g.nz + 1, kStreamRowsMin);
     return (size_t)((g.nx + v.cols - 1) / v.cols) * ((g.nz - 1 + v.rows - 1) / v.rows);
 }
 
@@ -195,7 +209,7 @@ size_t tiles_of(const eig_grid& g, const StencilVariant& v) {
 void stencil_candidates(const eig_ctx* c, int kind, bool one_step, std::vector<int>& out) {
     out.clear();
     if (c->forced_variant >= 0 && kVariants[c->forced_variant].medium_kind == kind &&
-        !kVariants[c->forced_variant].resident &&
+        !kVariants[c->forced_variant].resident && !kVariants[c->forced_variant].absorbing &&
         !(one_step && kVariants[c->forced_variant].steps != 1)) {
         out.push_back(c->forced_variant);
         return;
@@ -261,7 +275,10 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                 l.push_back({grids[solves[i].grid].nx, grids[solves[i].grid].nz, 1});
         if (!l.empty()) cd.assign(1, small_launch_variant(cd[0], l));
     }
+    static const std::vector<int> abs_cand = {kAbsorbingStream};
     auto cand_of = [&](int i) -> const std::vector<int>& {
+        const SolveSpec& sp = solves[i];
+        if (!res[i] && absorbing_stream(c, sp, grids[sp.grid], media[sp.medium])) return abs_cand;
         if (res[i]) return res_cand[media[solves[i].medium].kind];
         return cands[media[solves[i].medium].kind][one_step(i) ? 1 : 0];
     };
@@ -321,8 +338,9 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
         }
     }
     // one aligned piece per descriptor table, job table, receiver map and
-    // (halo) tile map: at most 4 solve classes x 2 maps x every variant
-    const size_t npieces = 4 + 8 * (size_t)kNumVariants;
+    // (halo) tile map: at most 8 solve classes with several candidates (those
+    // that are not resident), one map each but for rigid grids' halos
+    const size_t npieces = 4 + 8 * kMapVariants;
     size_t blob_bound = align_up((size_t)n * sizeof(SolveDesc)) +
                         align_up(ntiles_total * sizeof(int2)) + npieces * kAlign +
                         align_up((size_t)n * sizeof(SourceJob)) + 4 * kAlign;
@@ -357,9 +375,10 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
     for (int i = 0; i < n; ++i) {
         if (!kVariants[cand_of(i)[0]].stream) continue;
         const eig_grid& g = grids[solves[i].grid];
+        const int nz = g.nz + kVariants[cand_of(i)[0]].absorbing;
         auto& l = loads[class_of(i)];
-        if (!l.empty() && l.back().nx == g.nx && l.back().nz == g.nz) l.back().solves += 1;
-        else l.push_back({g.nx, g.nz, 1});
+        if (!l.empty() && l.back().nx == g.nx && l.back().nz == nz) l.back().solves += 1;
+        else l.push_back({g.nx, nz, 1});
     }
     for (int oi = 0; oi < n; ++oi) {
         const int i = ord[oi];
@@ -439,7 +458,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
             }
             if (sv.stream) {
                 const auto strips = stream_strips(g.nx, gr.cut.narrow, sv.steps);
-                for (int ch = 0; ch < stream_chunks(g.nz, gr.cut.rows); ++ch)
+                for (int ch = 0; ch < stream_chunks(g.nz + sv.absorbing, gr.cut.rows); ++ch)
                     for (const auto& st : strips)
                         gr.tiles[v].push_back(stream_tile(oi, st, ch));
                 gr.steps_tiles[v].push_back({g.nsteps, (int)gr.tiles[v].size()});
@@ -520,7 +539,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
             launch_nodal_coef(mk.rho, mk.lam, mk.mu, mk.nx, mk.nz, pitch_of(mk.nx), mk.h,
                               mk.dt, coef, s);
         else
-            launch_layered_coef(mk.rho, mk.lam, mk.mu, mk.nz, mk.h, mk.dt, coef, s);
+            launch_layered_coef(mk.rho, mk.lam, mk.mu, mk.nz, mk.h, mk.dt, mk.ce, coef, s);
     }
     launch_source_tables((const SourceJob*)(bd + o_jobs), n, 0, s);
     launch_fill_zero(base + fields_begin, fields_end - fields_begin, s);
@@ -651,6 +670,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                                    g.cand[vi], g.cut.rows, ls);
                 if (slot >= 0) HIP_TRY(hipEventRecord(tn.ev[2 * slot + 1], s));
                 if (g.bc == EIG_BC_ABSORBING && !replay && !resident &&
+                    !kVariants[g.cand[vi]].stream &&
                     !(kVariants[g.cand[vi]].edges && c->fused_edges))
                     launch_ce_edges(ddesc + g.first, nrun, step, ls);
                 c->launches += launch_units(kVariants[g.cand[vi]], step, stv.front().first);
@@ -722,18 +742,29 @@ struct WaveSizer {
     const std::vector<MediumKey>& media;
     const std::vector<RecSet>& recsets;
     std::vector<char> med_seen, rec_seen;
-    size_t bytes = (64 + 8 * kNumVariants) * kAlign;
+    size_t bytes = (64 + 8 * kMapVariants) * kAlign;
     WaveSizer(const std::vector<eig_grid>& g, const std::vector<MediumKey>& m,
               const std::vector<RecSet>& r)
         : grids(g), media(m), recsets(r), med_seen(m.size(), 0), rec_seen(r.size(), 0) {}
     size_t cost(const SolveSpec& sp) const {
         const eig_grid& g = grids[sp.grid];
         size_t b = solve_bytes(g) + sizeof(SolveDesc) + sizeof(SourceJob) + 64;
-        for (int v = 0; v < kNumVariants; ++v)
-            b += (tiles_of(g, kVariants[v]) + edge_tiles_of(g.nx, g.nz)) * sizeof(int2);
+        // tile maps: a solve's candidates are variants of one family, one of
+        // them where that takes four or more steps per launch
+        size_t maps[5] = {};
+        for (int v = 0; v < kNumVariants; ++v) {
+            const StencilVariant& sv = kVariants[v];
+            if (sv.medium_kind != media[sp.medium].kind) continue;
+            size_t& m = maps[sv.family()];
+            const size_t map =
+                (tiles_of(g, sv) + (sv.edges ? edge_tiles_of(g.nx, g.nz) : 0)) * sizeof(int2);
+            m = sv.family() == 4 ? std::max(m, map) : m + map;
+        }
         // three-step halo: side buffer and halo tile maps (upper bound)
         const size_t nb = (size_t)(g.nx + 127) / 128;
-        b += nb * g.nz * 4 * sizeof(float2) + 2 * nb * ((g.nz + 63) / 64) * sizeof(int2) + kAlign;
+        maps[3] += nb * g.nz * 4 * sizeof(float2) + 2 * nb * ((g.nz + 63) / 64) * sizeof(int2) +
+                   kAlign;
+        b += *std::max_element(maps, maps + 5);
         if (!med_seen[sp.medium]) b += medium_bytes(media[sp.medium]);
         if (!rec_seen[sp.recset]) b += 2 * align_up((size_t)pitch_of(recsets[sp.recset].nx) * 4);
         return b;
@@ -754,7 +785,8 @@ int validate_medium(const eig_medium& m) {
 
 int medium_index(std::vector<MediumKey>& media, std::map<MediumKey, int>& seen,
                  const eig_medium& m, const eig_grid& g) {
-    MediumKey k{m.kind, m.rho, m.lam, m.mu, g.nx, g.nz, g.h, g.dt};
+    MediumKey k{m.kind, m.rho, m.lam, m.mu, g.nx, g.nz, g.h, g.dt,
+                m.kind == EIG_MEDIUM_LAYERED && g.bc == EIG_BC_ABSORBING};
     auto it = seen.find(k);
     if (it != seen.end()) return it->second;
     const int id = (int)media.size();
@@ -827,7 +859,8 @@ int eig_ctx_set_option(eig_ctx* c, const char* name, int64_t value) {
         c->autotune = value != 0;
         if (!c->autotune) c->tuned.clear();
     } else if (n == "default_variant") {
-        if (value < 0 || value >= kNumVariants || kVariants[value].resident)
+        if (value < 0 || value >= kNumVariants || kVariants[value].resident ||
+            kVariants[value].absorbing)
             return set_error(EIG_EINVAL, "variant");
         c->default_variant = (int)value;
     } else if (n == "temporal_blocking") {

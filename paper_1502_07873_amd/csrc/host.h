@@ -218,9 +218,10 @@ struct MediumKey {
     const double *rho, *lam, *mu;
     int nx, nz;
     double h, dt;
+    bool ce = false;  // layered, absorbing edges: with the side columns' table
     bool operator<(const MediumKey& o) const {
-        return std::tie(kind, rho, lam, mu, nx, nz, h, dt) <
-               std::tie(o.kind, o.rho, o.lam, o.mu, o.nx, o.nz, o.h, o.dt);
+        return std::tie(kind, rho, lam, mu, nx, nz, h, dt, ce) <
+               std::tie(o.kind, o.rho, o.lam, o.mu, o.nx, o.nz, o.h, o.dt, o.ce);
     }
 };
 
@@ -246,7 +247,7 @@ inline int check_receivers(const eig_receivers& r, const eig_grid& g) {
 inline size_t solve_bytes(const eig_grid& g) {
     const size_t field = (size_t)g.nz * pitch_of(g.nx) * sizeof(float2);
     return align_up(field) * 4 + align_up(2 * kSrcW * kSrcW * sizeof(float)) +
-           align_up((size_t)std::max(g.nsteps, 1) * sizeof(float)) + 4 * kAlign;
+           align_up((size_t)std::max(g.nsteps, 1) * sizeof(float));
 }
 
 // Offset of a medium's table in its medium_bytes (aligned as they are).
@@ -255,7 +256,7 @@ inline size_t medium_table(int kind) { return kind == EIG_MEDIUM_NODAL ? 0 : kCo
 inline size_t medium_bytes(const MediumKey& k) {
     if (k.kind == EIG_MEDIUM_NODAL)
         return align_up((size_t)3 * k.nz * pitch_of(k.nx) * sizeof(float)) + kAlign;
-    return align_up((size_t)k.nz * kCoefStride * sizeof(float)) + 2 * kCoefPad + kAlign;
+    return align_up(layered_table_floats(k.nz, k.ce) * sizeof(float)) + kCoefPad + kAlign;
 }
 
 

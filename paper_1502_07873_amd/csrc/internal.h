@@ -20,7 +20,16 @@ constexpr int kCoefStride = 16;  // floats per row of a layered coefficient tabl
 // Readable bytes kept before and after a layered coefficient table: the
 // streaming kernels read the rows of levels that have not reached the grid's
 // first row yet, or have left its last, and drop what they form with them.
-constexpr size_t kCoefPad = 16 * kCoefStride * sizeof(float);
+constexpr int kCoefPadRows = 12;
+constexpr size_t kCoefPad = kCoefPadRows * kCoefStride * sizeof(float);
+// After the layered table of a grid with absorbing edges and its pad, the
+// streaming kernel's table of the side columns: per row, in FP64, 1 / (1 + a_p)
+// and 1 / (1 + a_s) (ce.h).
+constexpr int kCeStride = 4;  // floats
+constexpr size_t ce_table(int nz) { return (size_t)(nz + kCoefPadRows) * kCoefStride; }
+constexpr size_t layered_table_floats(int nz, bool ce) {
+    return ce_table(nz) + (ce ? (size_t)(nz + kCoefPadRows) * kCeStride : 0);
+}
 
 // Coefficient slots of a layered table row (all pre-multiplied by
 // dt^2 / (rho_k h^2) except kFco = dt^2 / rho_k for the body force).
@@ -74,7 +83,7 @@ struct SolveDesc {
 };
 
 // Leapfrog steps per launch of the streaming kernels (even).
-constexpr int kStreamSteps = 8, kNodalStreamSteps = 6;
+constexpr int kStreamSteps = 8, kNodalStreamSteps = 6, kAbsorbingStreamSteps = 6;
 
 // One forcing table to build (FP64 arithmetic, FP32 result).
 struct SourceJob {
@@ -141,7 +150,7 @@ int noalloc_scratch_init(int device);
 // launchers (all asynchronous on `s`)
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 void launch_layered_coef(const double* rho, const double* lam, const double* mu,
-                         int nz, double h, double dt, float* coef, hipStream_t s);
+                         int nz, double h, double dt, bool ce, float* coef, hipStream_t s);
 void launch_nodal_coef(const double* rho, const double* lam, const double* mu,
                        int nx, int nz, int pitch, double h, double dt, float* coef,
                        hipStream_t s);
@@ -157,6 +166,7 @@ struct StencilVariant {
     int resident;  // 1: one workgroup per solve, fields in LDS, all steps in one launch
     int forced_only;  // 1: runs only when forced (not a tuning candidate)
     int stream;       // 1: streams strips of rows through registers (stream.hip)
+    int absorbing;    // 1: a stream variant for absorbing edges
     // the temporal_blocking value that selects it
     int family() const { return steps >= 4 ? 4 : steps; }
 };
@@ -167,7 +177,7 @@ constexpr int kEdgeTileNodes = 128;
 inline int edge_tiles_of(int nx, int nz) {
     return (2 * nz + nx - 2 + kEdgeTileNodes - 1) / kEdgeTileNodes;
 }
-constexpr int kNumVariants = 28;
+constexpr int kNumVariants = 29;
 extern const StencilVariant kVariants[kNumVariants];
 // tiles: (solve index, strip << 16 | chunk) per wavefront
 // (rows: rows per tile of the stream variants)
@@ -203,7 +213,9 @@ inline std::vector<StreamStrip> stream_strips(int nx, int all_narrow, int K) {
         x0 += w - 2 * K;
     }
 }
+// (absorbing grids have one more row to form: nz + 1 in the place of nz)
 inline int stream_chunks(int nz, int rows) { return (nz - 1 + rows - 1) / rows; }
+constexpr int kAbsorbingStream = 28;
 inline int2 stream_tile(int solve, StreamStrip st, int chunk) {
     return make_int2(solve, (int)((unsigned)(st.x0 / 2) << 17 | (unsigned)st.narrow << 16 |
                                   (unsigned)chunk));
@@ -222,7 +234,7 @@ int small_launch_variant(int v, const std::vector<StreamLoad>& loads);
 void launch_nodal_stream(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
                          int rows, hipStream_t s);
 void launch_layered_stream(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
-                           int rows, hipStream_t s);
+                           int rows, int absorbing, hipStream_t s);
 // Nodal-media variants (6, 17..20) of launch_stencil.
 void launch_nodal_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
                           int variant, hipStream_t s);

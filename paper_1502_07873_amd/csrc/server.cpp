@@ -368,7 +368,7 @@ int srv_admit_group(eig_server* v, SrvQuery& q, hipStream_t s, bool* ok) {
                               pitch_of(g.nx), g.h, g.dt, (float*)(base + o_coef), s);
         else
             launch_layered_coef(q.medium.rho, q.medium.lam, q.medium.mu, g.nz, g.h, g.dt,
-                                (float*)(base + o_coef), s);
+                                false, (float*)(base + o_coef), s);
         launch_source_tables((const SourceJob*)(base + o_jobs), (int)gr.nslot, 0, s);
         launch_fill_zero(base + fields_begin, fields_end - fields_begin, s);
         launch_zero_level0(v->descs + gr.slot0, (int)gr.nslot, s);
@@ -624,7 +624,7 @@ int eig_server_create(eig_ctx* c, size_t budget, int32_t group_samples, eig_serv
     // media take two steps (16-row tiles under the cache limit) and nodal
     // media one, with two nodes per lane
     const int fv = c->forced_variant;
-    const bool forced = fv >= 0 && !kVariants[fv].resident;
+    const bool forced = fv >= 0 && !kVariants[fv].resident && !kVariants[fv].absorbing;
     const bool forced_layered = forced && kVariants[fv].medium_kind == EIG_MEDIUM_LAYERED;
     const bool forced_nodal = forced && kVariants[fv].medium_kind == EIG_MEDIUM_NODAL;
     v->cache_bytes = c->serve_cache_bytes;

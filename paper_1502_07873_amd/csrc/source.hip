@@ -261,7 +261,7 @@ __global__ void source_kernel(const SourceJob* __restrict__ jobs) {
 __global__ void layered_coef_kernel(const double* __restrict__ rho,
                                     const double* __restrict__ lam,
                                     const double* __restrict__ mu, int nz, double h,
-                                    double dt, float* __restrict__ coef) {
+                                    double dt, bool with_ce, float* __restrict__ coef) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nz) return;
     double c[kCoefStride];
@@ -302,6 +302,10 @@ __global__ void layered_coef_kernel(const double* __restrict__ rho,
         c[kCeL] = lam[k] * dt / (rho[k] * cp * h);
     }
     for (int j = 0; j < kCoefStride; ++j) coef[(size_t)k * kCoefStride + j] = (float)c[j];
+    if (!with_ce) return;
+    double* r = (double*)(coef + ce_table(nz) + (size_t)k * kCeStride);
+    r[0] = 1.0 / (1.f + (float)c[kCeP]);
+    r[1] = 1.0 / (1.f + (float)c[kCeS]);
 }
 
 __global__ void nodal_coef_kernel(const double* __restrict__ rho,
@@ -425,8 +429,8 @@ void launch_source_tables(const SourceJob* jobs, int njobs, int /*max_nsteps*/,
 }
 
 void launch_layered_coef(const double* rho, const double* lam, const double* mu,
-                         int nz, double h, double dt, float* coef, hipStream_t s) {
-    layered_coef_kernel<<<(nz + 127) / 128, 128, 0, s>>>(rho, lam, mu, nz, h, dt, coef);
+                         int nz, double h, double dt, bool ce, float* coef, hipStream_t s) {
+    layered_coef_kernel<<<(nz + 127) / 128, 128, 0, s>>>(rho, lam, mu, nz, h, dt, ce, coef);
 }
 
 void launch_nodal_coef(const double* rho, const double* lam, const double* mu,

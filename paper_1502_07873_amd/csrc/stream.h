@@ -100,6 +100,7 @@ struct StreamTile {
     int x0, col;               // the strip's and the lane's first column (within the pitch)
     bool st_ok;                // the lane stores its nodes
     bool free_col[N];          // columns 1..nx-2
+    bool left, right;          // the lane holds column 0 / nx-1
     const int* rec;            // the strip's receivers, -1 where none (LDS)
     int sk0, si0;              // forcing window: first row and column
     const float* sw;           // forcing tables (LDS)
@@ -132,6 +133,8 @@ __device__ __forceinline__ void tile_init(StreamTile<K, N>& t, const SolveDesc* 
     t.si0 = d->src_i0;
     t.sw = sw;
     t.rec = rec;
+    t.left = col == 0;
+    t.right = col <= nx - 1 && col + N > nx - 1;
 #pragma unroll
     for (int q = 0; q < N; ++q) {
         const int c = col + q;
@@ -166,7 +169,7 @@ __device__ __forceinline__ int lane_col(const StreamTile<K, N>& t) {
 }
 
 // The field rows a tile reads, three pipeline rows ahead: row i of u^m and row
-// i - 1 of u^{m-1}, both held at the grid's last ones.
+// i - 1 of u^{m-1}, held at the grid's last ones.
 template <int N>
 struct RowFeed {
     const float2 *cur, *prev;
@@ -189,11 +192,13 @@ struct RowFeed {
         cur += 2 * pitch;
         prev += pitch;
     }
-    // row i is done: its slot takes row i + 3
+    // row i is done: its slot takes row i + 3 (of prev, i + 2: rigid grids do not
+    // need its last row)
+    template <bool ABS = false>
     __device__ __forceinline__ void next(int i, int slot) {
         const size_t inc = i + 3 < nz ? pitch : 0;
         cur += inc;
-        prev += inc;
+        prev += ABS ? (i + 2 < nz ? pitch : 0) : inc;
         c[slot] = ld_pt<N>(cur, col);
         p[slot] = ld_pt<N>(prev, col);
     }
@@ -225,7 +230,8 @@ struct StreamEntry {
     int m, pin, x0, kb, ke;
     bool narrow;
 };
-template <int K>
+// (absorbing grids: the last row is formed as well)
+template <int K, bool ABS = false>
 __device__ __forceinline__ bool stream_entry(const SolveDesc* descs, int2 te, int pass, int rows,
                                              StreamEntry& e) {
     e.d = descs + __builtin_amdgcn_readfirstlane(te.x);
@@ -236,7 +242,7 @@ __device__ __forceinline__ bool stream_entry(const SolveDesc* descs, int2 te, in
     e.x0 = (int)(sc >> 17) * 2;
     e.narrow = (sc & 0x10000) != 0;
     e.kb = (int)(sc & 0xffff) * rows;
-    e.ke = min(e.kb + rows, e.d->nz - 1);
+    e.ke = min(e.kb + rows, e.d->nz - (ABS ? 0 : 1));
     return L >= 0 && e.m < e.d->nsteps;
 }
 

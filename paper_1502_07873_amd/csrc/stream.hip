@@ -53,26 +53,97 @@ __device__ __forceinline__ LayerCoef scalar_coef(ScalarRow c) {
     for (int j = 0; j < kFco; ++j) r.c[j] = c[j];
     return r;
 }
+// What the edge relation takes of a row.
+struct CeRow {
+    float ap, as, l;
+    double rp, rs;  // 1 / (1 + ap), 1 / (1 + as)
+};
+// (c: the coefficients' row, t: the side columns')
+__device__ __forceinline__ CeRow scalar_ce(ScalarRow c, ScalarRow t) {
+    const CAS double* r = (const CAS double*)t;
+    return {c[kCeP], c[kCeS], c[kCeL], r[0], r[1]};
+}
 
-// Levels 0..K-1 of a strip as seen between two rows: level j holds its row
-// i - 1 - j in c and the row above in p, with their x-differences.
 template <int K, int N>
 struct StreamState {
     Pt<N> c[K], p[K], dc[K], dp[K];
 };
 
+// What a strip holds of the grid's sides.  Rigid: columns that stay zero or
+// none.  Absorbing: column 0 (node 0 of a lane) and / or column nx-1 (node R of
+// a lane, -1: not in the strip), which follow the edge relation.
+template <bool EDGE>
+struct RigidSides {
+    static constexpr bool kAbs = false, kEdge = EDGE;
+};
+template <bool L, int R>
+struct AbsorbingSides {
+    static constexpr bool kAbs = true, kEdge = L || R >= 0, kLeft = L;
+    static constexpr int kRight = R;
+};
+
+// The side columns of an absorbing strip (the relation of ce.h, ce_side):
+// `below` and `above` are the column's rows r + 1 and r - 1 and half 1/2 (at the
+// ends of a side column: the one-sided difference and 1).  x / (1 + a) is x
+// times the FP64 reciprocal, rounded to FP32: the bits of the FP32 division,
+// because a quotient of two FP32 numbers is no closer than 2^-48 of itself to
+// where the rounding changes, and the product is off by 2^-52.  It takes 3
+// instructions, a division 10.
+template <int K, int N, class S>
+__device__ __forceinline__ void absorbing_columns(const StreamTile<K, N>& t, const CeRow& ce,
+                                                  float half, const Pt<N>& below,
+                                                  const Pt<N>& above, const Pt<N>& c,
+                                                  const Pt<N>& old, Pt<N>& nw) {
+#pragma clang fp contract(off)
+    float lu[N], ru[N], lv[N], rv[N];
+    x_neighbours<N>(c.u, lu, ru);
+    x_neighbours<N>(c.v, lv, rv);
+    auto edge = [](float a, double r, float prev, float in, float tang) {
+        return (float)(__builtin_fmaf(1.f - a, prev, 2.f * __builtin_fmaf(a, in, tang)) * r);
+    };
+    auto side = [&](auto q, float sg, float iu, float iv, bool here) {
+        constexpr int Q = decltype(q)::value;
+        const float dzu = half * (below.u[Q] - above.u[Q]), dzv = half * (below.v[Q] - above.v[Q]);
+        const float wu = edge(ce.ap, ce.rp, old.u[Q], iu, sg * ce.l * dzv);
+        const float wv = edge(ce.as, ce.rs, old.v[Q], iv, sg * ce.as * dzu);
+        nw.u[Q] = here ? wu : nw.u[Q];
+        nw.v[Q] = here ? wv : nw.v[Q];
+    };
+    if constexpr (S::kLeft) side(std::integral_constant<int, 0>(), 1.f, ru[0], rv[0], t.left);
+    if constexpr (S::kRight >= 0) {
+        constexpr int Q = S::kRight;
+        side(std::integral_constant<int, Q>(), -1.f, lu[Q], lv[Q], t.right);
+    }
+}
+
 // Level j's row r off the plain path: the surface row's own-row terms, the
-// forcing, rows past the grid's and rigid columns (zero), and the receivers.
-// a: the acceleration without the first two.
-template <int K, int N, bool EDGE>
+// forcing, the grid's last row (rigid: zero; absorbing: the edge relation) and
+// rows past it, the side columns, and the receivers.  a: the acceleration
+// without the first two.
+template <int K, int N, class S>
 __device__ __forceinline__ void stream_special(const StreamTile<K, N>& t, int j, int r,
-                                               const LayerCoef& cf, const Pt<N>& c,
-                                               const Pt<N>& dc, const Pt<N>& up, float2 (&a)[N],
-                                               Pt<N>& nw) {
-    if (r < 0 || r >= t.nz - 1) {
+                                               ScalarRow crow, const LayerCoef& cf,
+                                               const CeRow& ce, const Pt<N>& n, const Pt<N>& c,
+                                               const Pt<N>& p, const Pt<N>& dc, const Pt<N>& up,
+                                               float2 (&a)[N], Pt<N>& nw) {
+    if (r < 0 || r >= t.nz - (S::kAbs ? 0 : 1)) {
 #pragma unroll
         for (int q = 0; q < N; ++q) nw.u[q] = nw.v[q] = 0.f;
         return;
+    }
+    if constexpr (S::kAbs) {
+        if (r == t.nz - 1) {
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const float2 w = ce_bottom(crow[kCeP], crow[kCeS], crow[kCeL], dc.u[q], dc.v[q],
+                                           make_float2(p.u[q], p.v[q]),
+                                           make_float2(up.u[q], up.v[q]));
+                nw.u[q] = w.x;
+                nw.v[q] = w.y;
+            }
+            if constexpr (S::kEdge) absorbing_columns<K, N, S>(t, ce, 1.f, c, p, c, up, nw);
+            return;
+        }
     }
     const int col = lane_col(t);
     const int dk = r - t.sk0;
@@ -96,22 +167,33 @@ __device__ __forceinline__ void stream_special(const StreamTile<K, N>& t, int j,
             nw.v[q] = w.y;
         }
     }
-    if constexpr (EDGE) zero_rigid<K, N>(t, nw);
+    if constexpr (S::kAbs && S::kEdge) {
+        if (r == 0)
+            absorbing_columns<K, N, S>(t, ce, 1.f, n, c, c, up, nw);
+        else
+            absorbing_columns<K, N, S>(t, ce, 0.5f, n, p, c, up, nw);
+    } else if constexpr (S::kEdge) {
+        zero_rigid<K, N>(t, nw);
+    }
     if (r == 0 && t.m + j <= t.nsteps) record_row<K, N>(t, j, nw);
 }
 
 // One row of the pipeline: level 0 takes row i (`n`, with u^{m-1} one row up
 // in `up`), level j forms its row i - j from levels j-1 and j-2.  plain: every
-// level is on a free row below the surface, off the forcing window.  EDGE: the
-// strip has a rigid column.  cf_next: level 1's coefficients, for the next row
-// on return.
-template <int K, int N, bool EDGE>
+// level is on a free row below the surface, off the forcing window.  S: the strip's
+// side columns.  cf_next, ce_next: level 1's coefficients, for the next row on
+// return.
+template <int K, int N, class S>
 __device__ __forceinline__ void stream_row(const StreamTile<K, N>& t, StreamState<K, N>& s, int i,
-                                           bool plain, LayerCoef& cf_next, Pt<N> n, Pt<N> up) {
+                                           bool plain, LayerCoef& cf_next, CeRow& ce_next, Pt<N> n,
+                                           Pt<N> up) {
     // row i of the table; opaque, so that equal rows of two levels are loaded
     // twice rather than held in scalar registers between rows of the pipeline
     ScalarRow ci = (ScalarRow)((uintptr_t)t.coef + (intptr_t)i * (kCoefStride * sizeof(float)));
     __asm__ volatile("" : "+s"(ci));
+    ScalarRow ti = (ScalarRow)((uintptr_t)(t.coef + ce_table(t.nz)) +
+                               (intptr_t)i * (kCeStride * sizeof(float)));
+    if constexpr (S::kAbs && S::kEdge) __asm__ volatile("" : "+s"(ti));
 #pragma unroll
     for (int j = 1; j <= K; ++j) {
         const int r = i - j;
@@ -121,6 +203,10 @@ __device__ __forceinline__ void stream_row(const StreamTile<K, N>& t, StreamStat
         // a wait for one is a wait for all) and before this level's work
         __asm__ volatile("" ::"s"(cf.c[0]));
         cf_next = scalar_coef(ci - (j < K ? (j + 1) * kCoefStride : 0));
+        const CeRow ce = ce_next;
+        if constexpr (S::kAbs && S::kEdge)
+            ce_next = scalar_ce(ci - (j < K ? (j + 1) * kCoefStride : 0),
+                                ti - (j < K ? (j + 1) * kCeStride : 0));
         __builtin_amdgcn_sched_barrier(0);
         const Pt<N> dn = x_diff<N>(n), c = s.c[j - 1], p = s.p[j - 1], sx = x_sum<N>(c);
         Pt<N> nw;
@@ -145,12 +231,25 @@ __device__ __forceinline__ void stream_row(const StreamTile<K, N>& t, StreamStat
             nw.u[q] = w.x;
             nw.v[q] = w.y;
         }
-        if constexpr (EDGE) zero_rigid<K, N>(t, nw);
+        if constexpr (S::kAbs && S::kEdge) {
+            if (plain) absorbing_columns<K, N, S>(t, ce, 0.5f, n, p, c, up, nw);
+        } else if constexpr (S::kEdge) {
+            zero_rigid<K, N>(t, nw);
+        }
         if (__builtin_expect(!plain, 0))
-            stream_special<K, N, EDGE>(t, j, r, cf, c, s.dc[j - 1], up, a, nw);
+            stream_special<K, N, S>(t, j, r, ci - j * kCoefStride, cf, ce, n, c, p, s.dc[j - 1], up, a, nw);
         if (j == K && (unsigned)(r - t.kb) < (unsigned)t.nstore && t.st_ok) {
-            st_pt<N>(t.out1 + (size_t)r * t.pitch, t.col, c);
-            st_pt<N>(t.out0 + (size_t)r * t.pitch, t.col, nw);
+            Pt<N> w1 = c, w0 = nw;
+            if constexpr (S::kAbs && N == 2) {
+                if constexpr (S::kRight == 0) {  // the padding column beside nx-1 stays zero
+                    w1.u[1] = t.right ? 0.f : w1.u[1];
+                    w1.v[1] = t.right ? 0.f : w1.v[1];
+                    w0.u[1] = t.right ? 0.f : w0.u[1];
+                    w0.v[1] = t.right ? 0.f : w0.v[1];
+                }
+            }
+            st_pt<N>(t.out1 + (size_t)r * t.pitch, t.col, w1);
+            st_pt<N>(t.out0 + (size_t)r * t.pitch, t.col, w0);
         }
         up = p;
         s.p[j - 1] = c;
@@ -161,7 +260,7 @@ __device__ __forceinline__ void stream_row(const StreamTile<K, N>& t, StreamStat
     }
 }
 
-template <int K, int N, bool EDGE>
+template <int K, int N, class S>
 __device__ __forceinline__ void stream_strip(const StreamEntry& e, const float* sw, int* rec) {
     StreamTile<K, N> t;
     tile_init<K, N>(t, e.d, e.m, e.pin, e.x0, e.kb, e.ke, sw, rec);
@@ -170,13 +269,27 @@ __device__ __forceinline__ void stream_strip(const StreamEntry& e, const float* 
     RowFeed<N> f;
     f.init(e.d, e.pin, i0, t.col);
     LayerCoef cf = scalar_coef((ScalarRow)((uintptr_t)t.coef) + ((ptrdiff_t)i0 - 1) * kCoefStride);
+    CeRow ce{};
+    if constexpr (S::kAbs && S::kEdge)
+        ce = scalar_ce((ScalarRow)((uintptr_t)t.coef) + ((ptrdiff_t)i0 - 1) * kCoefStride,
+                       (ScalarRow)((uintptr_t)(t.coef + ce_table(t.nz))) +
+                           ((ptrdiff_t)i0 - 1) * kCeStride);
     for (int i = i0; i < i1; i += 3) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            stream_row<K, N, EDGE>(t, s, i + q, plain_row(t, i + q), cf, f.c[q], f.p[q]);
-            f.next(i + q, q);
+            stream_row<K, N, S>(t, s, i + q, plain_row(t, i + q), cf, ce, f.c[q], f.p[q]);
+            f.template next<S::kAbs>(i + q, q);
         }
     }
+}
+
+template <int K>
+__device__ __forceinline__ void load_tables(const StreamEntry& e, float* sw) {
+    load_forcing<K>(e.d, e.m, sw);
+    if (threadIdx.x < kSrcW)
+        sw[kSwFco + threadIdx.x] =
+            ld1(e.d->coef, (size_t)(e.d->src_k0 + threadIdx.x) * kCoefStride + kFco);
+    __syncthreads();
 }
 
 template <int K>
@@ -189,24 +302,68 @@ stencil_layered_stream(const SolveDesc* __restrict__ descs, const int2* __restri
     if (b >= ntiles) return;
     StreamEntry e;
     if (!stream_entry<K>(descs, tiles[b], pass, rows, e)) return;  // uniform
-    load_forcing<K>(e.d, e.m, sw);
-    if (threadIdx.x < kSrcW)
-        sw[kSwFco + threadIdx.x] =
-            ld1(e.d->coef, (size_t)(e.d->src_k0 + threadIdx.x) * kCoefStride + kFco);
-    __syncthreads();
+    load_tables<K>(e, sw);
     if (e.narrow)
-        stream_strip<K, 1, true>(e, sw, rec);
+        stream_strip<K, 1, RigidSides<true>>(e, sw, rec);
     else if (e.x0 == 0 || e.x0 + 128 > e.d->nx - 1)
-        stream_strip<K, 2, true>(e, sw, rec);
+        stream_strip<K, 2, RigidSides<true>>(e, sw, rec);
     else
-        stream_strip<K, 2, false>(e, sw, rec);
+        stream_strip<K, 2, RigidSides<false>>(e, sw, rec);
+}
+
+// The same with absorbing edges (variant 28): the side strips form their side
+// columns in the same pass, the last row is a special row, and the halo is that
+// of the rigid kernel (an edge node reads one node inside and two along the
+// edge).  What a strip has of the sides is its template, so that the inner
+// strips and each kind of side strip pay for what they hold only; the side
+// columns take 16 instructions a side and level for both components, against
+// 24 per update of all 128 columns.  Bound: vector issue, as above.  K = 6: 8
+// spills registers.  Against one step per launch (edge nodes in extra
+// wavefronts; launch-bound up to some 60 solves of 252 x 90, field bytes above),
+// us per step on 252 x 90: 1 solve 8.9 -> 4.4, 30 9.3 -> 6.2, 60 10.6 -> 9.4, 104
+// 13.5 -> 13.0, 195 22.8 -> 13.9; 512 solves of 201 x 151 79 -> 31.  No measured
+// load is faster with one step, so no rule keeps it.
+template <int K>
+__global__ void __launch_bounds__(64, 2)
+stencil_absorbing_stream(const SolveDesc* __restrict__ descs, const int2* __restrict__ tiles,
+                         int ntiles, int pass, int rows) {
+    __shared__ float sw[kSwSeries + K];
+    __shared__ int rec[128];
+    const int b = xcd_block(blockIdx.x, gridDim.x);
+    if (b >= ntiles) return;
+    StreamEntry e;
+    if (!stream_entry<K, true>(descs, tiles[b], pass, rows, e)) return;  // uniform
+    load_tables<K>(e, sw);
+    const int nx = e.d->nx;
+    const bool left = e.x0 == 0, right = e.x0 + (e.narrow ? 64 : 128) > nx - 1;
+    const bool odd = (nx - 1) & 1;  // column nx-1 is a lane's second node
+    if (e.narrow) {
+        if (left && right) stream_strip<K, 1, AbsorbingSides<true, 0>>(e, sw, rec);
+        else if (left) stream_strip<K, 1, AbsorbingSides<true, -1>>(e, sw, rec);
+        else if (right) stream_strip<K, 1, AbsorbingSides<false, 0>>(e, sw, rec);
+        else stream_strip<K, 1, AbsorbingSides<false, -1>>(e, sw, rec);
+    } else if (left && right) {
+        if (odd) stream_strip<K, 2, AbsorbingSides<true, 1>>(e, sw, rec);
+        else stream_strip<K, 2, AbsorbingSides<true, 0>>(e, sw, rec);
+    } else if (left) {
+        stream_strip<K, 2, AbsorbingSides<true, -1>>(e, sw, rec);
+    } else if (right) {
+        if (odd) stream_strip<K, 2, AbsorbingSides<false, 1>>(e, sw, rec);
+        else stream_strip<K, 2, AbsorbingSides<false, 0>>(e, sw, rec);
+    } else {
+        stream_strip<K, 2, AbsorbingSides<false, -1>>(e, sw, rec);
+    }
 }
 
 }  // namespace
 
 void launch_layered_stream(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
-                           int rows, hipStream_t s) {
-    if (ntiles > 0)
+                           int rows, int absorbing, hipStream_t s) {
+    if (ntiles <= 0) return;
+    if (absorbing)
+        stencil_absorbing_stream<kAbsorbingStreamSteps><<<ntiles, 64, 0, s>>>(
+            descs, tiles, ntiles, pass, rows);
+    else
         stencil_layered_stream<kStreamSteps><<<ntiles, 64, 0, s>>>(descs, tiles, ntiles, pass,
                                                                    rows);
 }

@@ -39,6 +39,7 @@ const StencilVariant kVariants[kNumVariants] = {
     {64, 24, EIG_MEDIUM_NODAL, 4, 0, 0, 1},  // 25: as 27, operands read per node (forced only)
     {58, 58, EIG_MEDIUM_LAYERED, 4, 0, 0, 1},  // 26: four steps, tile in LDS (small launches)
     {58, 34, EIG_MEDIUM_NODAL, 4, 0, 0, 1},  // 27: the same, nodal: tile and medium in LDS
+    {0, 0, EIG_MEDIUM_LAYERED, kAbsorbingStreamSteps, 0, 0, 1, 1, 1},  // 28: as 23, absorbing edges
 };
 
 void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
@@ -47,7 +48,7 @@ void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int s
     if (kVariants[variant].stream && kVariants[variant].medium_kind == EIG_MEDIUM_NODAL)
         launch_nodal_stream(descs, tiles, ntiles, step, rows, s);
     else if (kVariants[variant].stream)
-        launch_layered_stream(descs, tiles, ntiles, step, rows, s);
+        launch_layered_stream(descs, tiles, ntiles, step, rows, kVariants[variant].absorbing, s);
     else if (kVariants[variant].steps == 4)
         launch_blocked_stencil(descs, tiles, ntiles, step, variant, s);
     else if (kVariants[variant].medium_kind == EIG_MEDIUM_NODAL)

@@ -71,3 +71,28 @@ def test_strips_and_chunks(kind, variant, base, nx, nz, solves):
             ref = elastic.forward(g, med, th[0], rec)
             assert np.max(np.abs(ref)) > 0
             check_receivers(a[0], ref, TRACE_TOL, what=f"{kind} {nx}x{nz}")
+
+
+# absorbing edges: both sides in one strip, a lane's first or second node on the
+# right side, sides in different strips, narrow and wide, a last row of its own
+@pytest.mark.parametrize("nx,nz,solves", [(8, 8, 2), (64, 9, 3), (65, 17, 3), (128, 25, 3),
+                                          (129, 33, 2), (168, 24, 2), (169, 41, 2), (200, 18, 400),
+                                          (201, 50, 400), (129, 49, 400)])
+def test_absorbing_strips_and_chunks(nx, nz, solves):
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    rng = np.random.default_rng(nx * 100 + nz)
+    h = 10.0
+    med = synthetic.random_layers_medium(rng, nz, h, 2)
+    rec = np.unique(np.r_[1, 2, 55, 56, 57, 63, 64, 127, 128, nx - 3, nx - 2])
+    rec = rec[rec <= nx - 2].astype(np.int32)
+    for nsteps in (1, 5, 6, 7, 48) if solves < 100 else (49,):
+        g = synthetic.Grid(nx, nz, h, synthetic.cfl_dt(h, med.vp_max()), nsteps, bc="absorbing")
+        th = _thetas(g, solves, rng)
+        print(f"[gpu case] absorbing stream {nx}x{nz}x{nsteps}, {solves} solves", flush=True)
+        a, b = _run(28, g, med, th, rec), _run(1, g, med, th, rec)
+        assert np.array_equal(a, b), nsteps
+        if nsteps >= 48:
+            ref = elastic.forward(g, med, th[0], rec)
+            assert np.max(np.abs(ref)) > 0
+            check_receivers(a[0], ref, TRACE_TOL, what=f"absorbing {nx}x{nz}")
