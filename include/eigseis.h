@@ -462,8 +462,10 @@ int design_greedy(eig_ctx* ctx, int32_t nsample, int32_t ncand,
  *   w:     DEVICE [nsample] weights
  *   order, curve: device [kmax], as for design_greedy
  * Scratch: a 64 MiB static device array per GPU (held until the process
- * ends), of which a call uses about 8 * nsample * (ncand + 49) + 9 * ncand
+ * ends), of which a call uses about 8 * nsample * (ncand + 49) + 8 * ncand
  * bytes plus 1 KiB; EIG_EBUDGET, before any launch, if that exceeds 64 MiB.
+ * Where 8 n (n + 1) / 2 bytes per sample and candidate (n inferred parameters)
+ * fit beside that, they hold a packed copy of H1r, which is faster to read.
  * Every call on one GPU shares that GPU's array: calls that overlap on one
  * GPU (different streams or host threads) race and must be serialised by
  * the caller.  The context's own workspace is not touched.

@@ -1611,7 +1611,7 @@ int theorem3_eig(eig_ctx* c, int32_t nsample, const eig_grid* grid, const eig_me
     if ((rc = upload_small(c, o_pr, prior, sizeof(eig_prior), s))) return rc;
     if ((rc = upload_small(c, o_th, th_cur.data(), th_cur.size() * sizeof(double), s))) return rc;
     if ((rc = upload_small(c, o_w, w, (size_t)nsample * sizeof(double), s))) return rc;
-    launch_theorem3(H1out, H2out, nsample, (const eig_prior*)(c->ws + o_pr),
+    launch_theorem3(H1out, H2out, nsample, prior->active, (const eig_prior*)(c->ws + o_pr),
                     (const double*)(c->ws + o_th), (const double*)(c->ws + o_w), val, status,
                     eig, s);
     HIP_TRY(hipGetLastError());
@@ -1641,8 +1641,9 @@ int laplace_eig(eig_ctx* c, int32_t nsample, const double* H1, const eig_prior* 
     if ((rc = upload_small(c, o_pr, prior, sizeof(eig_prior), s))) return rc;
     if ((rc = upload_small(c, o_th, th.data(), th.size() * sizeof(double), s))) return rc;
     if ((rc = upload_small(c, o_w, w, (size_t)nsample * sizeof(double), s))) return rc;
-    launch_laplace(H1, nsample, (const eig_prior*)(c->ws + o_pr), (const double*)(c->ws + o_th),
-                   (const double*)(c->ws + o_w), dkl, logdet, status, eig, s);
+    launch_laplace(H1, nsample, prior->active, (const eig_prior*)(c->ws + o_pr),
+                   (const double*)(c->ws + o_th), (const double*)(c->ws + o_w), dkl, logdet,
+                   status, eig, s);
     HIP_TRY(hipGetLastError());
     return EIG_OK;
 }
@@ -1671,9 +1672,9 @@ int design_eval(eig_ctx* c, int32_t nsample, int32_t ncand, const double* H1r,
     if ((rc = upload_small(c, o_pr, prior, sizeof(eig_prior), s))) return rc;
     if ((rc = upload_small(c, o_th, th.data(), th.size() * sizeof(double), s))) return rc;
     if ((rc = upload_small(c, o_w, w, (size_t)nsample * sizeof(double), s))) return rc;
-    launch_design_eval(H1r, nsample, ncand, mask, ndesign, (const eig_prior*)(c->ws + o_pr),
-                       (const double*)(c->ws + o_th), (const double*)(c->ws + o_w),
-                       (double*)(c->ws + o_work), eig, s);
+    launch_design_eval(H1r, nsample, ncand, mask, ndesign, prior->active,
+                       (const eig_prior*)(c->ws + o_pr), (const double*)(c->ws + o_th),
+                       (const double*)(c->ws + o_w), (double*)(c->ws + o_work), eig, s);
     HIP_TRY(hipGetLastError());
     return EIG_OK;
 }
@@ -1694,25 +1695,23 @@ int design_greedy(eig_ctx* c, int32_t nsample, int32_t ncand, const double* H1r,
     const size_t o_pr = cv.take(sizeof(eig_prior));
     const size_t o_th = cv.take((size_t)nsample * kNT * sizeof(double));
     const size_t o_w = cv.take((size_t)nsample * sizeof(double));
-    const size_t o_work = cv.take((size_t)nsample * ncand * sizeof(double));
-    const size_t o_ival = cv.take((size_t)ncand * sizeof(double));
-    const size_t o_H = cv.take((size_t)nsample * kNT * kNT * sizeof(double));
-    const size_t o_ch = cv.take((size_t)ncand);
-    rc = ensure_ws(c, cv.off);
-    if (rc) return rc;
+    size_t scratch = greedy_scratch(nsample, ncand);
+    const size_t o_work = cv.take(scratch * sizeof(double));
+    // the packed Hessians where the budget has room for them
+    const size_t more = greedy_packed(nsample, ncand, prior->active);
+    if (cv.off + more * sizeof(double) <= c->budget &&
+        ensure_ws(c, cv.off + more * sizeof(double)) == EIG_OK)
+        scratch += more;
+    else if ((rc = ensure_ws(c, cv.off)))
+        return rc;
     std::vector<double> th((size_t)nsample * kNT, 0.0);
     if (theta) std::memcpy(th.data(), theta, th.size() * sizeof(double));
     if ((rc = upload_small(c, o_pr, prior, sizeof(eig_prior), s))) return rc;
     if ((rc = upload_small(c, o_th, th.data(), th.size() * sizeof(double), s))) return rc;
     if ((rc = upload_small(c, o_w, w, (size_t)nsample * sizeof(double), s))) return rc;
-    launch_fill_zero(c->ws + o_H, (size_t)nsample * kNT * kNT * sizeof(double), s);
-    launch_fill_zero(c->ws + o_ch, (size_t)ncand, s);
-    for (int k = 0; k < kmax; ++k)
-        launch_greedy_step(H1r, nsample, ncand, (const eig_prior*)(c->ws + o_pr),
-                           (const double*)(c->ws + o_th), (const double*)(c->ws + o_w),
-                           (double*)(c->ws + o_H), (uint8_t*)(c->ws + o_ch),
-                           (double*)(c->ws + o_work), (double*)(c->ws + o_ival), k, order,
-                           curve, s);
+    launch_greedy(H1r, nsample, ncand, prior->active, (const eig_prior*)(c->ws + o_pr),
+                  (const double*)(c->ws + o_th), (const double*)(c->ws + o_w),
+                  (double*)(c->ws + o_work), scratch, kmax, order, curve, s);
     HIP_TRY(hipGetLastError());
     return EIG_OK;
 }

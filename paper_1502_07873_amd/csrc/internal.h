@@ -294,18 +294,27 @@ inline size_t receiver_work_doubles(int nt, int nrec) {
 void launch_hessian(const SampleDesc* samples, int nsample, int per_receiver,
                     int ngroup, const double* sigma, double* H1, double* work, hipStream_t s,
                     size_t receiver_stride = 0);
-void launch_laplace(const double* H1, int nsample, const eig_prior* prior_dev,
+// active: the prior's mask of inferred parameters (0: all).
+void launch_laplace(const double* H1, int nsample, int active, const eig_prior* prior_dev,
                     const double* theta, const double* w, double* dkl,
                     double* logdet, int32_t* status, double* eig, hipStream_t s);
 void launch_design_eval(const double* H1r, int nsample, int ncand,
-                        const uint8_t* mask, int ndesign,
+                        const uint8_t* mask, int ndesign, int active,
                         const eig_prior* prior_dev, const double* theta,
                         const double* w, double* work, double* eig, hipStream_t s);
-void launch_greedy_step(const double* H1r, int nsample, int ncand,
-                        const eig_prior* prior_dev, const double* theta,
-                        const double* w, double* Hcur, uint8_t* chosen,
-                        double* work, double* ival, int k, int32_t* order,
-                        double* curve, hipStream_t s);
+// Doubles of scratch that the greedy search takes at least, and those of the
+// packed Hessians that make it faster.
+inline size_t greedy_scratch(int nsample, int ncand) {
+    return (size_t)nsample * (ncand + kNT * kNT) + ncand;
+}
+inline size_t greedy_packed(int nsample, int ncand, int active) {
+    const int n = active ? __builtin_popcount(active) : kNT;
+    return (size_t)nsample * ncand * (n * (n + 1) / 2);
+}
+void launch_greedy(const double* H1r, int nsample, int ncand, int active,
+                   const eig_prior* prior_dev, const double* theta, const double* w,
+                   double* scratch, size_t scratch_doubles, int kmax, int32_t* order, double* curve,
+                   hipStream_t s);
 void launch_surface_peak(const float2* traces, int count, double rel,
                          double* out, hipStream_t s);
 void launch_h2(const H2Job* jobs, int njobs, hipStream_t s);
@@ -314,7 +323,7 @@ void launch_h2(const H2Job* jobs, int njobs, hipStream_t s);
 // s = 0..N-1 (traces [N+1][nrec]); max_elems = the largest N * nrec.
 void launch_dual_force(const DualJob* jobs, int njobs, size_t max_elems, hipStream_t s);
 // Theorem 3 integrand per sample and the weighted average.
-void launch_theorem3(const double* H1, const double* H2, int nsample,
+void launch_theorem3(const double* H1, const double* H2, int nsample, int active,
                      const eig_prior* prior_dev, const double* theta_hat, const double* w,
                      double* val, int32_t* status, double* eig, hipStream_t s);
 

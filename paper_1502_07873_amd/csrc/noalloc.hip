@@ -1,10 +1,10 @@
 // Greedy receiver selection for callers that cannot allocate device memory
 // (code under HIP graph capture, tight serving loops, harnesses that forbid
 // hipMalloc).  Same kernels and reduction order as design_greedy; the
-// scratch it needs (the prior, per-(sample, candidate) D^_KL values, the
-// candidates' weighted sums, the running per-sample Hessian and the chosen
-// flags) lives in one file-scope device array instead of the context's
-// workspace, and the caller's inputs are device arrays.
+// scratch it needs (the prior, the running per-sample Hessians, the
+// candidates' weighted sums and, for many samples, D^_KL of every pair) lives
+// in one file-scope device array instead of the context's workspace, and the
+// caller's inputs are device arrays.
 #include <mutex>
 
 #include "host.h"
@@ -28,17 +28,14 @@ __global__ void store_prior_kernel(eig_prior p, eig_prior* dst) { *dst = p; }
 
 // Bytes the greedy search keeps in scratch, each piece 256-byte aligned.
 struct ScratchPlan {
-    size_t o_prior, o_work, o_ival, o_H, o_ch, end;
+    size_t o_prior, o_work, end;
 };
 
 ScratchPlan plan(int nsample, int ncand) {
     Carve cv;
     ScratchPlan p;
     p.o_prior = cv.take(sizeof(eig_prior));
-    p.o_work = cv.take((size_t)nsample * ncand * sizeof(double));
-    p.o_ival = cv.take((size_t)ncand * sizeof(double));
-    p.o_H = cv.take((size_t)nsample * kNT * kNT * sizeof(double));
-    p.o_ch = cv.take((size_t)ncand);
+    p.o_work = cv.take(greedy_scratch(nsample, ncand) * sizeof(double));
     p.end = cv.off;
     return p;
 }
@@ -95,17 +92,12 @@ int design_greedy_noalloc(eig_ctx* c, int32_t nsample, int32_t ncand, const doub
     hipStream_t s = (hipStream_t)stream;
     eig_prior* dprior = (eig_prior*)(base + sp.o_prior);
     store_prior_kernel<<<1, 1, 0, s>>>(*prior, dprior);
-    // the running Hessians and the chosen flags start at zero (kernels, not
-    // memset: the call may be captured into a graph)
-    launch_fill_zero(base + sp.o_H, (size_t)nsample * kNT * kNT * sizeof(double), s);
-    launch_fill_zero(base + sp.o_ch, (size_t)ncand, s);
     // theta is only read for a Gaussian prior; a uniform prior's kernels get
     // a valid address they never dereference
     const double* th = theta ? theta : (const double*)(base + sp.o_work);
-    for (int k = 0; k < kmax; ++k)
-        launch_greedy_step(H1r, nsample, ncand, dprior, th, w, (double*)(base + sp.o_H),
-                           (uint8_t*)(base + sp.o_ch), (double*)(base + sp.o_work),
-                           (double*)(base + sp.o_ival), k, order, curve, s);
+    launch_greedy(H1r, nsample, ncand, prior->active, dprior, th, w,
+                  (double*)(base + sp.o_work), (kScratchBytes - sp.o_work) / sizeof(double),
+                  kmax, order, curve, s);
     HIP_TRY(hipGetLastError());
     return EIG_OK;
 }

@@ -434,7 +434,7 @@ int srv_finish_query(eig_server* v, SrvQuery& q, hipStream_t s) {
     const size_t o_w = blob.put(q.w.data(), q.w.size() * sizeof(double));
     int rc = upload(c, base, blob.data, s);
     if (rc) return rc;
-    launch_laplace(q.H1, q.nsample, (const eig_prior*)(base + o_pr),
+    launch_laplace(q.H1, q.nsample, q.prior.active, (const eig_prior*)(base + o_pr),
                    (const double*)(base + o_th), (const double*)(base + o_w), q.dkl, nullptr,
                    q.chol_status, q.eig, s);
     HIP_TRY(hipEventRecord(q.done_ev, s));
