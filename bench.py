@@ -44,8 +44,8 @@ CSRC = os.path.join(ROOT, "paper_1502_07873_amd", "csrc")
 LAYERED_SOURCES = ("stencil.hip", "node_update.h", "tile.h")
 NODAL_SOURCES = ("nodal.hip", "node_update.h", "tile.h")
 BLOCKED_SOURCES = ("stream.hip", "stream_nodal.hip", "stream.h", "blocked.hip", "node_update.h",
-                   "tile.h")   # variants 23-27
-RESIDENT_SOURCES = ("resident.hip", "node_update.h", "ce.h")
+                   "tile.h")   # variants 23-28
+RESIDENT_SOURCES = ("resident.hip", "stream.h", "node_update.h", "ce.h")
 
 
 def _sources_sha(*names):
@@ -90,15 +90,15 @@ BLOCKED_FLOOR_B = 32.0 / 4
 
 def _kernel_sources(variant, tiled):
     """The sources of a stencil variant's kernel: `tiled` unless it is one of
-    the four-step kernels with the tile in LDS."""
-    return BLOCKED_SOURCES if variant in (23, 24, 25, 26, 27) else tiled
+    the streaming or four-step kernels."""
+    return BLOCKED_SOURCES if variant in (23, 24, 25, 26, 27, 28) else tiled
 
 
 def _steps_per_launch(variant):
     """Leapfrog steps one launch of a stencil variant takes."""
     if variant in (15, 16):
         return 3
-    if variant in (23, 24, 25, 26, 27):   # the launch count's unit
+    if variant in (23, 24, 25, 26, 27, 28):   # the launch count's unit
         return 4
     return 2 if (9 <= variant <= 14 or variant in (19, 20)) else 1
 

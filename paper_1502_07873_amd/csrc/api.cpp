@@ -363,6 +363,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
         int kind, bc, cls;
         int first, last;               // solve range in launch order
         size_t lds = 0;                // resident groups: dynamic LDS bytes
+        int rcls = 0;                  // and their grids' largest class
         StreamCut cut;                 // stream variants
         std::vector<int> cand;         // candidate variants
         std::vector<std::vector<int2>> tiles;                     // per candidate
@@ -453,7 +454,9 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
             if (sv.resident) {
                 gr.tiles[v].push_back(make_int2(oi, g.bc == EIG_BC_ABSORBING ? 1 : 0));
                 gr.steps_tiles[v].push_back({g.nsteps, (int)gr.tiles[v].size()});
-                gr.lds = std::max(gr.lds, resident_lds_bytes(mk.kind, g.nx, g.nz));
+                const bool ab = g.bc == EIG_BC_ABSORBING;
+                gr.rcls = std::max(gr.rcls, resident_class(g.nx, g.nz, ab));
+                gr.lds = std::max(gr.lds, resident_lds_used(mk.kind, g.nx, g.nz, ab));
                 continue;
             }
             if (sv.stream) {
@@ -664,7 +667,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                 }
                 if (!replay && resident)
                     launch_resident(ddesc, (const int2*)(bd + o_tiles[gi][vi]), ntile, g.kind,
-                                    g.lds, ls);
+                                    g.rcls, g.lds, ls);
                 else if (!replay)
                     launch_stencil(ddesc, (const int2*)(bd + o_tiles[gi][vi]), ntile, step,
                                    g.cand[vi], g.cut.rows, ls);

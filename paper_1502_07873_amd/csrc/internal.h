@@ -251,7 +251,32 @@ inline size_t resident_lds_bytes(int kind, int nx, int nz) {
     return (size_t)nx * nz * 2 * sizeof(float2) + kResSrcwFloats * sizeof(float) +
            (kind == EIG_MEDIUM_LAYERED ? (size_t)nz * kCoefStride * sizeof(float) : 0);
 }
-void launch_resident(const SolveDesc* descs, const int2* tiles, int ntiles, int kind,
+// Depth-only resident grids by the kernel that takes them (resident.hip): 0 and 1
+// keep the fields in registers (0: one column per lane and few rows, in 64
+// registers, which leaves room for a second workgroup on a CU), 2 in LDS: more
+// columns than a wave holds, or more rows than 128 registers do (from 11 rows a
+// wave on, one column per lane, and from 7, two, they spill).
+constexpr int kResWaves = 16;
+constexpr int kResRows1Small = 6, kResRows1 = 10, kResRows2 = 6;  // rows of a wave at most
+__host__ __device__ inline int resident_columns(int nx, bool absorbing) {
+    return (absorbing ? nx : nx - 2) <= 64 ? 1 : 2;
+}
+__host__ __device__ inline int resident_class(int nx, int nz, bool absorbing) {
+    const int rows = (nz - 1 + kResWaves - 1) / kResWaves;
+    if ((absorbing ? nx : nx - 2) > 128) return 2;
+    if (resident_columns(nx, absorbing) == 2) return rows <= kResRows2 ? 1 : 2;
+    return rows <= kResRows1Small ? 0 : rows <= kResRows1 ? 1 : 2;
+}
+// LDS of such a solve.
+inline size_t resident_lds_used(int kind, int nx, int nz, bool absorbing) {
+    if (kind != EIG_MEDIUM_LAYERED || resident_class(nx, nz, absorbing) == 2)
+        return resident_lds_bytes(kind, nx, nz);
+    const size_t rows = (size_t)(kResWaves + 2) * 2 * 64 * resident_columns(nx, absorbing);
+    return 2 * (rows + (absorbing ? 4 * nz : 0)) * sizeof(float2) + 64 * sizeof(float2) +
+           (absorbing ? (size_t)nz * 32 : 0);
+}
+// cls: the largest class of the tiles' grids (depth-only media)
+void launch_resident(const SolveDesc* descs, const int2* tiles, int ntiles, int kind, int cls,
                      size_t lds_bytes, hipStream_t s);
 // Halo values of the three-steps-per-launch kernels; htiles: (solve,
 // boundary << 16 | 64-row chunk).

@@ -15,6 +15,20 @@ namespace {
 // of its rows (depth-only media), and the series values of the K steps.
 constexpr int kSwFco = 2 * kSrcW * kSrcW, kSwSeries = kSwFco + kSrcW;
 
+// A row of a coefficient table through the scalar cache.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define CAS __attribute__((address_space(4)))
+#else
+#define CAS
+#endif
+typedef const CAS float* ScalarRow;
+__device__ __forceinline__ LayerCoef scalar_coef(ScalarRow c) {
+    LayerCoef r;
+#pragma unroll
+    for (int j = 0; j < kFco; ++j) r.c[j] = c[j];
+    return r;
+}
+
 // N neighbouring nodes of one row held by a lane.
 template <int N>
 struct Pt {

@@ -40,19 +40,6 @@ namespace eig {
 
 namespace {
 
-// A row of a coefficient table through the scalar cache.
-#if defined(__HIP_DEVICE_COMPILE__)
-#define CAS __attribute__((address_space(4)))
-#else
-#define CAS
-#endif
-typedef const CAS float* ScalarRow;
-__device__ __forceinline__ LayerCoef scalar_coef(ScalarRow c) {
-    LayerCoef r;
-#pragma unroll
-    for (int j = 0; j < kFco; ++j) r.c[j] = c[j];
-    return r;
-}
 // What the edge relation takes of a row.
 struct CeRow {
     float ap, as, l;
