@@ -17,10 +17,14 @@
 // K u (|y_n|^2 + |g_m|^2) / (2 sigma^2) nats in a log ratio: ~1e-9 nats for
 // traces of ~100 sigma over K ~ 200 values, ~1e-5 at ~3000 sigma.
 //
-// Work decomposition: a 512-thread block (8 waves, 4 x 2) owns 128 outer rows
+// Work decomposition: a block of 4 waves (2 x 2) owns 64 outer rows
 // and a range of inner samples (the range is split over several blocks when
 // the rows alone cannot fill the chip), swept in tiles of 128 columns; each
-// wave accumulates 2 x 4 MFMA tiles (32 rows x 64 columns).  A first pass
+// wave accumulates 2 x 4 MFMA tiles (32 rows x 64 columns).  Two such blocks
+// share a CU, so that one's sums and barriers run beside the other's MFMA: 73.4 ms
+// at 1e5 x 1e5 x 204 (55.6 TFLOP/s, the matrix cores 72 % busy at the 2.15 GHz
+// that this load runs at) against 75.6 with one block of 8 waves and 128 rows; the
+// rest goes to the sums' FP64 instructions.  Few rows take blocks of 32 or 16.  A first pass
 // writes y and g as FP64, k-major and zero-padded to whole tiles and chunks
 // (Yt[k][n], Gt[k][m]); k is then staged through LDS in chunks of 16 with
 // 16-byte copies and nothing else (no conversion, no bounds), double
@@ -41,47 +45,67 @@ namespace {
 
 typedef double dv4 __attribute__((ext_vector_type(4)));
 
-// Tile geometry: 8 waves as kGR x kGC, each kWR x kWC 16x16 MFMA tiles.
-constexpr int kWR = 2, kWC = 4, kGR = 4, kGC = 2, kKC = 16;
-constexpr int kThreads = 64 * kGR * kGC;          // 512
-constexpr int kTN = 16 * kGR * kWR;               // 128 outer rows per block
+// Tile geometry: GR x kGC waves, each WR x kWC 16x16 MFMA tiles.  How many rows a
+// block takes changes no result: a row's columns are dealt to the same lanes in
+// the same order.
+constexpr int kWC = 4, kGC = 2, kKC = 16;
 constexpr int kTM = 16 * kGC * kWC;               // 128 inner columns per tile
-constexpr int kLY = kTN + 2, kLB = kTM + 2;       // padded LDS rows (16-byte aligned pairs)
-constexpr int kQY = kKC * kTN / (2 * kThreads);   // y pairs staged per thread and chunk
-constexpr int kQB = kKC * kTM / (2 * kThreads);   // g pairs staged per thread and chunk
 constexpr int kNP = 16 * kGC;                     // per-row partials in a block
-constexpr int kBuf = kKC * (kLY + kLB);
-constexpr int kLds = 2 * kBuf > 2 * kNP * kTN ? 2 * kBuf : 2 * kNP * kTN;
-static_assert(2 * kQY * kThreads == kKC * kTN && 2 * kQB * kThreads == kKC * kTM,
-              "staging split");
+template <int WR, int GR>
+struct Geo {
+    static constexpr int kThreads = 64 * GR * kGC;
+    static constexpr int kTN = 16 * GR * WR;          // outer rows per block
+    static constexpr int kLY = kTN + 2, kLB = kTM + 2;  // padded LDS rows (16-byte aligned pairs)
+    static constexpr int kQY = kKC * kTN / (2 * kThreads);   // y pairs staged per thread and chunk
+    static constexpr int kQB = kKC * kTM / (2 * kThreads);   // g pairs staged per thread and chunk
+    static constexpr int kBuf = kKC * (kLY + kLB);
+    static constexpr int kLds = 2 * kBuf > 2 * kNP * kTN ? 2 * kBuf : 2 * kNP * kTN;
+    static_assert(2 * kQY * kThreads == kKC * kTN && 2 * kQB * kThreads == kKC * kTM,
+                  "staging split");
+};
+using Rows64 = Geo<2, 2>;
+using Rows32 = Geo<1, 2>;
+using Rows16 = Geo<1, 1>;
+constexpr int kTN = 128;                          // what the packed y are padded to
 typedef double dv2 __attribute__((ext_vector_type(2)));
 constexpr double kDrop = -40.0;                   // terms below max - 40 nats are dropped
 
-// Squared norms of y_n = g_n + sigma e_n (noise != NULL) or of g_m, one
-// wave per row, FP64.  The same fma forms y as the staging below.
-__global__ void __launch_bounds__(256)
-nested_sqnorm_kernel(const float* __restrict__ g, const float* __restrict__ noise, int rows,
-                     int nobs, double sigma, double* __restrict__ out) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
-    if (row >= rows) return;
-    double s = 0.0;
+// Squared norms of y_n = g_n + sigma e_n (noise != NULL) and of e_n, or of g_m,
+// one wave per row, FP64.  The same fma forms y as the packing below.
+__device__ __forceinline__ void nested_sqnorm(const float* __restrict__ g,
+                                              const float* __restrict__ noise, int row, int nobs,
+                                              double sigma, double* __restrict__ out,
+                                              double* __restrict__ out_noise) {
+    const int l = threadIdx.x & 63;
+    double s = 0.0, s2 = 0.0;
     for (int k = l; k < nobs; k += 64) {
         double y = (double)g[(size_t)row * nobs + k];
-        if (noise) y = fma(sigma, (double)noise[(size_t)row * nobs + k], y);
+        if (noise) {
+            const double e = (double)noise[(size_t)row * nobs + k];
+            y = fma(sigma, e, y);
+            s2 = fma(e, e, s2);
+        }
         s = fma(y, y, s);
     }
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (l == 0) out[row] = s;
+    for (int off = 32; off >= 1; off >>= 1) {
+        s += __shfl_xor(s, off, 64);
+        if (noise) s2 += __shfl_xor(s2, off, 64);
+    }
+    if (l == 0) {
+        out[row] = s;
+        if (noise) out_noise[row] = s2;
+    }
 }
 
 // out[k][r] (rows rpad apart, k < kpad) = y_r[k] = g_r[k] + sigma e_r[k]
 // (noise != NULL) or g_r[k], in FP64 (the same fma as the norms), zero for
 // r >= rows or k >= nobs.  32 x 32 tiles transposed through LDS.
-__global__ void __launch_bounds__(256)
-nested_pack_kernel(const float* __restrict__ g, const float* __restrict__ noise, int rows,
-                   int nobs, double sigma, int rpad, int kpad, double* __restrict__ out) {
+__device__ __forceinline__ void nested_pack(const float* __restrict__ g,
+                                            const float* __restrict__ noise, int bx, int by,
+                                            int rows, int nobs, double sigma, int rpad, int kpad,
+                                            double* __restrict__ out) {
     __shared__ double tile[32][33];
-    const int r0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
+    const int r0 = bx * 32, k0 = by * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     for (int j = ty; j < 32; j += 8) {
         const int r = r0 + j, k = k0 + tx;
@@ -99,16 +123,47 @@ nested_pack_kernel(const float* __restrict__ g, const float* __restrict__ noise,
     }
 }
 
-// Partial log-sum-exp of rows [n0, n0+128) over inner samples [mb, me):
+// One side's inputs (the outer data or the inner outputs) and what is made of them.
+struct NestedSide {
+    const float *g, *noise;
+    int rows, rpad;
+    double *norm, *noise_norm, *packed;
+};
+
+// Both sides' norms and packed copies in one launch (at 1000 samples, a quarter of
+// the time went to the gaps between four): the outer side's blocks come first, of
+// each side those that pack.
+__global__ void __launch_bounds__(256)
+nested_prepare_kernel(NestedSide outer, NestedSide inner, int nobs, double sigma, int kpad) {
+    const int kb = (kpad + 31) / 32;
+    int b = blockIdx.x;
+    const int nb_outer = outer.rpad / 32 * kb + (outer.rows + 3) / 4;
+    const NestedSide& s = b < nb_outer ? outer : inner;
+    if (b >= nb_outer) b -= nb_outer;
+    const int tiles = s.rpad / 32;
+    if (b < tiles * kb) {
+        nested_pack(s.g, s.noise, b % tiles, b / tiles, s.rows, nobs, sigma, s.rpad, kpad,
+                    s.packed);
+        return;
+    }
+    const int row = (b - tiles * kb) * 4 + (threadIdx.x >> 6);
+    if (row < s.rows) nested_sqnorm(s.g, s.noise, row, nobs, sigma, s.norm, s.noise_norm);
+}
+
+// Partial log-sum-exp of rows [n0, n0 + kTN) over inner samples [mb, me):
 // part_max / part_sum [split][nouter].  Yt, Gt: the packed y and g (rows
 // npad and mpad apart).
-__global__ void __launch_bounds__(kThreads)
+template <int WR, int GR>
+__global__ void __launch_bounds__(64 * GR * kGC, 2)
 nested_lse_kernel(const double* __restrict__ Yt, const double* __restrict__ Gt, int npad,
                   int mpad, const double* __restrict__ ynorm,
                   const double* __restrict__ gnorm, int nouter, int ninner, int nobs,
                   double inv2s2, int mchunk, double* __restrict__ part_max,
                   double* __restrict__ part_sum) {
-    __shared__ __attribute__((aligned(16))) double smem[kLds];
+    using G = Geo<WR, GR>;
+    constexpr int kWR = WR, kThreads = G::kThreads, kTN = G::kTN, kLY = G::kLY, kLB = G::kLB;
+    constexpr int kQY = G::kQY, kQB = G::kQB, kBuf = G::kBuf;
+    __shared__ __attribute__((aligned(16))) double smem[G::kLds];
     const int t = threadIdx.x, w = t >> 6, l = t & 63;
     const int wr = w / kGC, wc = w % kGC;
     // MFMA lane layout: operand lane (li, lk) holds row/column li of k-slice
@@ -262,24 +317,21 @@ nested_lse_kernel(const double* __restrict__ Yt, const double* __restrict__ Gt, 
     }
 }
 
-// Merge the inner-range partials (fixed order) into the log ratios.
-__global__ void nested_merge_kernel(const float* __restrict__ noise, int nouter, int ninner,
-                                    int nobs, int nsplit, const double* __restrict__ part_max,
+// Merge the inner-range partials (fixed order) into the log ratios, which hold
+// |e_n|^2 so far.
+__global__ void nested_merge_kernel(int nouter, int ninner, int nsplit,
+                                    const double* __restrict__ part_max,
                                     const double* __restrict__ part_sum,
                                     double* __restrict__ logratio) {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= nouter) return;
+    const double e2 = logratio[n];
     double M = -INFINITY;
     for (int c = 0; c < nsplit; ++c) M = fmax(M, part_max[(size_t)c * nouter + n]);
     double S = 0.0;
     for (int c = 0; c < nsplit; ++c) {
         const double pm = part_max[(size_t)c * nouter + n];
         if (pm > -INFINITY) S += part_sum[(size_t)c * nouter + n] * exp(pm - M);
-    }
-    double e2 = 0.0;
-    for (int k = 0; k < nobs; ++k) {
-        const double e = noise[(size_t)n * nobs + k];
-        e2 += e * e;
     }
     logratio[n] = -0.5 * e2 - (M + log(S) - log((double)ninner));
 }
@@ -314,13 +366,15 @@ size_t nested_workspace(int nouter, int ninner, int nobs) {
            kp * ((size_t)nested_rpad(nouter, kTN) + nested_rpad(ninner, kTM)) * sizeof(double);
 }
 
-// Inner-range splits, each at least two column tiles long: enough blocks to
+// Inner-range splits (of kTN rows, the unit of a block here whatever the rows a
+// block takes: the split decides a result's last bits), each at least two column
+// tiles long: enough blocks to
 // fill the chip when the outer rows are few, and a block count whose last
 // round of the chip's block slots is nearly full.  Every block of a launch
 // does the same work, so with b blocks on kSlots slots the launch takes
 // ceil(b / kSlots) rounds: 3125 blocks at N = 4e5 take 13 rounds for 12.2
 // rounds of work (6 % idle), 12500 take 49 for 48.8.
-constexpr int kSlots = 256;   // one block per CU: 8 waves of ~214 VGPRs fill its 4 SIMDs
+constexpr int kSlots = 256;   // one pair of blocks (kTN rows) per CU: 8 waves fill its 4 SIMDs
 int nested_splits(int nouter, int ninner) {
     const long rows = (nouter + kTN - 1) / kTN;
     auto fill = [&](long split) {
@@ -349,18 +403,29 @@ void launch_nested(const float* gout, const float* noise, const float* gin, int 
     const int kpad = nested_kpad(nobs);
     double* Yt = (double*)((char*)work + (head + 255) / 256 * 256);
     double* Gt = Yt + (size_t)kpad * npad;
-    nested_sqnorm_kernel<<<(nouter + 3) / 4, 256, 0, s>>>(gout, noise, nouter, nobs, sigma, ynorm);
-    nested_sqnorm_kernel<<<(ninner + 3) / 4, 256, 0, s>>>(gin, nullptr, ninner, nobs, 0.0, gnorm);
-    nested_pack_kernel<<<dim3(npad / 32, (kpad + 31) / 32), 256, 0, s>>>(
-        gout, noise, nouter, nobs, sigma, npad, kpad, Yt);
-    nested_pack_kernel<<<dim3(mpad / 32, (kpad + 31) / 32), 256, 0, s>>>(
-        gin, nullptr, ninner, nobs, 0.0, mpad, kpad, Gt);
-    const dim3 grid((nouter + kTN - 1) / kTN, split);
-    nested_lse_kernel<<<grid, kThreads, 0, s>>>(Yt, Gt, npad, mpad, ynorm, gnorm, nouter, ninner,
-                                                nobs, 1.0 / (2.0 * sigma * sigma), mchunk, pmax,
-                                                psum);
-    nested_merge_kernel<<<(nouter + 255) / 256, 256, 0, s>>>(noise, nouter, ninner, nobs,
-                                                             split, pmax, psum, logratio);
+    const NestedSide outer{gout, noise, nouter, npad, ynorm, logratio, Yt};
+    const NestedSide inner{gin, nullptr, ninner, mpad, gnorm, nullptr, Gt};
+    const int kb = (kpad + 31) / 32;
+    nested_prepare_kernel<<<npad / 32 * kb + (nouter + 3) / 4 + mpad / 32 * kb + (ninner + 3) / 4,
+                            256, 0, s>>>(outer, inner, nobs, sigma, kpad);
+    auto lse = [&](auto kernel, int rows, int threads) {
+        const dim3 grid((nouter + rows - 1) / rows, split);
+        kernel<<<grid, threads, 0, s>>>(Yt, Gt, npad, mpad, ynorm, gnorm, nouter, ninner, nobs,
+                                        1.0 / (2.0 * sigma * sigma), mchunk, pmax, psum);
+    };
+    // Rows per block: 64 where such blocks give every SIMD a wave, else 32, else
+    // 16 (a block's time goes with its rows, down to one wave per SIMD): 1000 x
+    // 1000 x 204 took 136 us in 16 blocks of 128 rows on 256 CUs, 62 in 126 of 16.
+    const int64_t waves64 = (int64_t)((nouter + Rows64::kTN - 1) / Rows64::kTN) * split * 4;
+    const int64_t waves32 = (int64_t)((nouter + Rows32::kTN - 1) / Rows32::kTN) * split * 4;
+    if (waves64 >= 4 * kSlots)
+        lse(nested_lse_kernel<2, 2>, Rows64::kTN, Rows64::kThreads);
+    else if (waves32 >= 4 * kSlots)
+        lse(nested_lse_kernel<1, 2>, Rows32::kTN, Rows32::kThreads);
+    else
+        lse(nested_lse_kernel<1, 1>, Rows16::kTN, Rows16::kThreads);
+    nested_merge_kernel<<<(nouter + 63) / 64, 64, 0, s>>>(nouter, ninner, split, pmax, psum,
+                                                          logratio);
     if (eig) mean_kernel<<<1, 256, 0, s>>>(logratio, nouter, eig);
 }
 
