@@ -84,8 +84,10 @@ def _measured_traffic(solves_per_launch, wave_cache_bytes, variant):
 
 # fields a four-step launch must move per update: each node's two levels
 # read once and written once per four steps (the tiles' halos, which
-# neighbouring tiles share, come mostly from L2)
+# neighbouring tiles share, come mostly from L2); the streaming kernels
+# take eight (23) or six steps per launch
 BLOCKED_FLOOR_B = 32.0 / 4
+STREAM_FLOOR_B = {23: 32.0 / 8, 24: 32.0 / 6, 28: 32.0 / 6}
 
 
 def _kernel_sources(variant, tiled):
@@ -397,8 +399,8 @@ def _bench_c3(nsample=4096, oracle_check=True):
     out.update(_leg_roofline(
         st, "24 B per grid-point update (read u^m, u^{m-1}, write u^{m+1}) over the stencil "
             "launch time, against the 8 TB/s HBM peak; " +
-            ("four steps per launch with the tile in LDS, one wave per grid and length "
-             "through HBM: the kernel moves about 8 B per update, so achieved can pass "
+            ("eight steps per launch in registers, one wave per grid and length "
+             "through HBM: the kernel moves about 4 B per update, so achieved can pass "
              "the peak" if four else
              "the waves run as cache-sized chunks, so the launches read and write the "
              "256 MB last-level cache (bound 'llc') and achieved may approach or pass the "
@@ -1169,7 +1171,7 @@ def main():
                                 variant)
     traffic_rate = traffic / (avg_launch_ms * 1e-3) / 1e9 if traffic else None
     in_cache = steps_per_launch < 4   # two or three steps: cache-sized chunks
-    floor_b = {1: 24.0, 2: 16.0, 3: 32.0 / 3.0, 4: BLOCKED_FLOOR_B}[steps_per_launch]
+    floor_b = {1: 24.0, 2: 16.0, 3: 32.0 / 3.0, 4: STREAM_FLOOR_B.get(variant, BLOCKED_FLOOR_B)}[steps_per_launch]
     status_ok = int(out["status"].abs().sum()) == 0 and int(out["chol_status"].abs().sum()) == 0
     line = {
         "metric": METRIC,
@@ -1202,8 +1204,9 @@ def main():
                     "time_frac_of_step": st["ms"] / total_ms,
                     "solves_per_launch": solves_per_launch,
                     "note": ("launches of the 15*S-solve jacobian_fd wave, every solve in "
-                             "every launch (four steps per launch with each 58x58 tile and "
-                             "its 4-node halo in LDS: the fields stream through HBM)"
+                             "every launch (eight steps per launch, streamed through "
+                             "registers and counted as two launches of four steps: the "
+                             "fields stream through HBM)"
                              if not in_cache else
                              "launches of the 15*S-solve jacobian_fd wave, run as chunks "
                              "whose fields (4 buffers per solve) fit wave_cache_bytes, so "
@@ -1227,8 +1230,8 @@ def main():
                      "note": "achieved: 24 B per update (algorithmic: read u^m, u^{m-1}, "
                              "write u^{m+1}) over the launch time; frac: achieved / the "
                              "8 TB/s HBM peak. " + (
-                                 "The kernel takes four steps per launch with the tile in "
-                                 "LDS, so it moves about 8 B per update, not 24: "
+                                 "The kernel takes eight steps per launch in registers, "
+                                 "so it moves about 4 B per update, not 24: "
                                  "achieved can pass the peak. traffic: bytes per launch "
                                  "past L2 from the counter record; frac_of_copy: that "
                                  "traffic rate over a plain 2 x 4 GiB copy measured in "

@@ -111,8 +111,8 @@ size_t live_field_bytes(const eig_ctx* c, const SolveSpec& sp, const eig_grid& g
 // by kind, grid and length, so that each chunk is one or two uniform groups
 // of launches.  Waves where fewer than cache_chunk_min_solves solves would
 // fit are not split for the cache (too few tiles per launch to pay).  Solves
-// that take four steps per launch with the tile in LDS move a quarter of the
-// two-step kernels' field bytes per step and run faster as one wave through
+// that take four or more steps per launch move a quarter or less of the one-step
+// kernels' field bytes per step and run faster as one wave through
 // HBM (all their tiles in every launch) than in cache-sized chunks, so their
 // fields do not count towards the limit.  A chunk also holds at most
 // max_wave_solves solves when that is set.

@@ -200,7 +200,7 @@ int srv_admit_group(eig_server* v, SrvQuery& q, hipStream_t s, bool* ok) {
                                    pitch_of(q.grid.nx) * sizeof(float2);
         // the cache limit applies to queries one of whose samples fits it;
         // larger ones gain nothing from it and are admitted by memory alone,
-        // and so are four-step kinds, which stream HBM at their floor
+        // and so are kinds with four or more steps per launch, which stream HBM
         const bool cached = v->cache_bytes && spl < 4 && sample_live <= v->cache_bytes;
         if (cached) {
             G = std::min<int>(G, (int)(v->cache_bytes / sample_live));
@@ -619,8 +619,8 @@ int eig_server_create(eig_ctx* c, size_t budget, int32_t group_samples, eig_serv
     v->group_samples = group_samples > 0 ? group_samples : 16;
     // the server advances groups launch by launch: resident variants (a
     // whole time loop per launch) are not used here.  Rigid edges only, so
-    // with temporal_blocking 4 (the default) both kinds take four steps per
-    // launch with the tile in LDS (variants 23, 24); otherwise depth-only
+    // with temporal_blocking 4 (the default) both kinds take six or eight steps
+    // per launch (variants 23, 24; small groups four, 26 and 27); otherwise depth-only
     // media take two steps (16-row tiles under the cache limit) and nodal
     // media one, with two nodes per lane
     const int fv = c->forced_variant;
