@@ -24,7 +24,8 @@
 // share a CU, so that one's sums and barriers run beside the other's MFMA: 73.4 ms
 // at 1e5 x 1e5 x 204 (55.6 TFLOP/s, the matrix cores 72 % busy at the 2.15 GHz
 // that this load runs at) against 75.6 with one block of 8 waves and 128 rows; the
-// rest goes to the sums' FP64 instructions.  Few rows take blocks of 32 or 16.  A first pass
+// rest goes to the sums' FP64 instructions.  Few rows take blocks of 32, or
+// of 16 whose two waves read their operands without LDS.  A first pass
 // writes y and g as FP64, k-major and zero-padded to whole tiles and chunks
 // (Yt[k][n], Gt[k][m]); k is then staged through LDS in chunks of 16 with
 // 16-byte copies and nothing else (no conversion, no bounds), double
@@ -59,7 +60,9 @@ struct Geo {
     static constexpr int kQY = kKC * kTN / (2 * kThreads);   // y pairs staged per thread and chunk
     static constexpr int kQB = kKC * kTM / (2 * kThreads);   // g pairs staged per thread and chunk
     static constexpr int kBuf = kKC * (kLY + kLB);
-    static constexpr int kLds = 2 * kBuf > 2 * kNP * kTN ? 2 * kBuf : 2 * kNP * kTN;
+    static constexpr bool kDirect = WR * GR == 1;  // no staging through LDS
+    static constexpr int kLds =
+        !kDirect && 2 * kBuf > 2 * kNP * kTN ? 2 * kBuf : 2 * kNP * kTN;
     static_assert(2 * kQY * kThreads == kKC * kTN && 2 * kQB * kThreads == kKC * kTM,
                   "staging split");
 };
@@ -220,32 +223,9 @@ nested_lse_kernel(const double* __restrict__ Yt, const double* __restrict__ Gt, 
         }
     };
     dv4 acc[kWR][kWC];
-    auto compute = [&](int c) {
-        const double* sY = smem + (c & 1) * kBuf;
-        const double* sB = sY + kKC * kLY;
-        const int kc = c % nk;
-        if (kc == 0) {
-#pragma unroll
-            for (int x = 0; x < kWR; ++x)
-#pragma unroll
-                for (int y = 0; y < kWC; ++y) acc[x][y] = dv4{0.0, 0.0, 0.0, 0.0};
-        }
-#pragma unroll
-        for (int ks = 0; ks < kKC / 4; ++ks) {
-            double a[kWR], b[kWC];
-#pragma unroll
-            for (int x = 0; x < kWR; ++x) a[x] = sY[(4 * ks + lk) * kLY + wr * 16 * kWR + 16 * x + li];
-#pragma unroll
-            for (int y = 0; y < kWC; ++y) b[y] = sB[(4 * ks + lk) * kLB + wc * 16 * kWC + 16 * y + li];
-#pragma unroll
-            for (int x = 0; x < kWR; ++x)
-#pragma unroll
-                for (int y = 0; y < kWC; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
-        }
-        if (kc != nk - 1) return;
-        // online log-sum-exp over this tile's columns
-        const int m0 = mb + (c / nk) * kTM;
+    // online log-sum-exp over a tile's columns
+    auto fold = [&](int tile) {
+        const int m0 = mb + tile * kTM;
         double gn[kWC];
         bool ok[kWC];
 #pragma unroll
@@ -279,19 +259,87 @@ nested_lse_kernel(const double* __restrict__ Yt, const double* __restrict__ Gt, 
                 sm[x][v] = s + (double)f;
             }
     };
+    auto compute = [&](int c) {
+        const double* sY = smem + (c & 1) * kBuf;
+        const double* sB = sY + kKC * kLY;
+        const int kc = c % nk;
+        if (kc == 0) {
+#pragma unroll
+            for (int x = 0; x < kWR; ++x)
+#pragma unroll
+                for (int y = 0; y < kWC; ++y) acc[x][y] = dv4{0.0, 0.0, 0.0, 0.0};
+        }
+#pragma unroll
+        for (int ks = 0; ks < kKC / 4; ++ks) {
+            double a[kWR], b[kWC];
+#pragma unroll
+            for (int x = 0; x < kWR; ++x) a[x] = sY[(4 * ks + lk) * kLY + wr * 16 * kWR + 16 * x + li];
+#pragma unroll
+            for (int y = 0; y < kWC; ++y) b[y] = sB[(4 * ks + lk) * kLB + wc * 16 * kWC + 16 * y + li];
+#pragma unroll
+            for (int x = 0; x < kWR; ++x)
+#pragma unroll
+                for (int y = 0; y < kWC; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
+        }
+        if (kc == nk - 1) fold(c / nk);
+    };
 
-    fetch(0, ry[0], rb[0]);
-    fetch(1, ry[1], rb[1]);
-    for (int c = 0; c < nchunks; c += 2) {
-        store(c, ry[0], rb[0]);
-        __syncthreads();
-        fetch(c + 2, ry[0], rb[0]);
-        compute(c);
-        if (c + 1 < nchunks) {
-            store(c + 1, ry[1], rb[1]);
+    if constexpr (G::kDirect) {
+        // Operands straight from the packed copies, a chunk ahead: where the
+        // device is not full, a wave has its SIMD to itself, and the LDS copy
+        // and its barriers only add to its chain (1000 x 1000 x 204, the whole
+        // estimate: 73 us with it, 64 without).
+        double a[2][kKC / 4], b[2][kKC / 4][kWC];
+        auto operands = [&](int c, int set) {
+            const double* y = Yt + (size_t)((c % nk) * kKC + lk) * npad + n0 + li;
+            const double* g = Gt + (size_t)((c % nk) * kKC + lk) * mpad + mb + (c / nk) * kTM +
+                              wc * 16 * kWC + li;
+#pragma unroll
+            for (int ks = 0; ks < kKC / 4; ++ks) {
+                a[set][ks] = y[(size_t)4 * ks * npad];
+#pragma unroll
+                for (int q = 0; q < kWC; ++q) b[set][ks][q] = g[(size_t)4 * ks * mpad + 16 * q];
+            }
+        };
+        auto multiply = [&](int c, int set) {
+            if (c % nk == 0) {
+#pragma unroll
+                for (int q = 0; q < kWC; ++q) acc[0][q] = dv4{0.0, 0.0, 0.0, 0.0};
+            }
+#pragma unroll
+            for (int ks = 0; ks < kKC / 4; ++ks)
+#pragma unroll
+                for (int q = 0; q < kWC; ++q)
+                    acc[0][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[set][ks], b[set][ks][q],
+                                                                     acc[0][q], 0, 0, 0);
+            if (c % nk == nk - 1) fold(c / nk);
+        };
+        if (nchunks > 0) operands(0, 0);
+        for (int c = 0; c < nchunks; c += 2) {
+            if (c + 1 < nchunks) operands(c + 1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(c, 0);
+            if (c + 1 < nchunks) {
+                if (c + 2 < nchunks) operands(c + 2, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(c + 1, 1);
+            }
+        }
+    } else {
+        fetch(0, ry[0], rb[0]);
+        fetch(1, ry[1], rb[1]);
+        for (int c = 0; c < nchunks; c += 2) {
+            store(c, ry[0], rb[0]);
             __syncthreads();
-            fetch(c + 3, ry[1], rb[1]);
-            compute(c + 1);
+            fetch(c + 2, ry[0], rb[0]);
+            compute(c);
+            if (c + 1 < nchunks) {
+                store(c + 1, ry[1], rb[1]);
+                __syncthreads();
+                fetch(c + 3, ry[1], rb[1]);
+                compute(c + 1);
+            }
         }
     }
     __syncthreads();
@@ -415,7 +463,7 @@ void launch_nested(const float* gout, const float* noise, const float* gin, int 
     };
     // Rows per block: 64 where such blocks give every SIMD a wave, else 32, else
     // 16 (a block's time goes with its rows, down to one wave per SIMD): 1000 x
-    // 1000 x 204 took 136 us in 16 blocks of 128 rows on 256 CUs, 62 in 126 of 16.
+    // 1000 x 204 took 136 us in 16 blocks of 128 rows on 256 CUs, some 50 in 126 of 16.
     const int64_t waves64 = (int64_t)((nouter + Rows64::kTN - 1) / Rows64::kTN) * split * 4;
     const int64_t waves32 = (int64_t)((nouter + Rows32::kTN - 1) / Rows32::kTN) * split * 4;
     if (waves64 >= 4 * kSlots)
