@@ -188,7 +188,7 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
  *                      device's 256 MB last-level cache (solves grouped by
  *                      grid and length); waves where fewer than
  *                      "cache_chunk_min_solves" solves would fit are not
- *                      split.  Solves taking four steps per launch do not
+ *                      split.  Solves taking four or more steps per launch do not
  *                      count (they run as one wave through HBM).  0: never
  *                      split for the cache.  Results do not depend on it.
  *   "cache_chunk_min_solves" 16 (default): see "wave_cache_bytes"; >= 1
@@ -206,7 +206,7 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
  *                      to fit; at least one group is always admitted), and
  *                      use 16-row tiles, so their launches work in the
  *                      last-level cache; queries with larger samples, and
- *                      every query of a kind that takes four steps per
+ *                      every query of a kind that takes four or more steps per
  *                      launch ("temporal_blocking" 4), are admitted by
  *                      memory alone.  0: admit whatever memory and slots
  *                      allow.  Results do not depend on it.
