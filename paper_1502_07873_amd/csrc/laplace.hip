@@ -64,6 +64,25 @@ __device__ __forceinline__ bool scaled_logdet(double (&a)[kTri<N>], double* out)
         m *= __builtin_amdgcn_frexp_mant(x);
         e += __builtin_amdgcn_frexp_exp(x);
     };
+    // Rows with a diagonal entry far down the range, the subnormals among them,
+    // are brought up by 2^256 each first (exactly): 1 / (s_i s_j) would overflow
+    // from s_i s_j = 2^-1024 on.
+    constexpr double kFarDown = 0x1p-960;
+    bool far = false;
+#pragma unroll
+    for (int j = 0; j < N; ++j) far = far || a[tri(j, j)] < kFarDown;
+    if (__builtin_expect(far, 0)) {
+        int up[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            up[i] = a[tri(i, i)] < kFarDown ? 256 : 0;
+            e -= up[i];
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) a[tri(i, j)] = ldexp(a[tri(i, j)], up[i] + up[j]);
+    }
 #pragma unroll
     for (int j = 0; j < N; ++j) {
         const double d = a[tri(j, j)];
