@@ -69,11 +69,12 @@ int family_steps_of(const eig_ctx* c, int kind, bool one_step) {
 }
 
 // Whether a solve with absorbing edges that is not resident streams several
-// steps per launch (variant 28): depth-only media, forward solves, unless a
-// variant, fewer steps per launch or the separate edge kernel is asked for.
+// steps per launch (variant 28): depth-only media with the side columns' table
+// (drop_side_table), forward solves, unless a variant, fewer steps per launch or
+// the separate edge kernel is asked for.
 bool absorbing_stream(const eig_ctx* c, const SolveSpec& sp, const eig_grid& g,
                       const MediumKey& mk) {
-    return g.bc == EIG_BC_ABSORBING && sp.rforce == nullptr && mk.kind == EIG_MEDIUM_LAYERED &&
+    return g.bc == EIG_BC_ABSORBING && sp.rforce == nullptr && mk.ce &&
            c->temporal_blocking == 4 && c->fused_edges &&
            (c->forced_variant < 0 || c->forced_variant == kAbsorbingStream);
 }
@@ -803,6 +804,17 @@ struct WaveSizer {
     }
 };
 
+// A wave of one solve (or of one sample's) that the budget does not hold goes
+// without the side columns' table and then takes one step per launch: the table
+// is 16 B per row, which on grids of some 8 x 6000 and taller is more than the
+// tile maps of one kernel leave of what every kernel's once took.  False: no
+// table to leave out (resident solves need theirs, 14 kB at most).
+bool drop_side_table(const eig_ctx* c, const eig_grid& g, MediumKey& m) {
+    if (!m.ce || resident_ok(c, g, m.kind)) return false;
+    m.ce = false;
+    return true;
+}
+
 int validate_medium(const eig_medium& m) {
     if (m.kind != EIG_MEDIUM_LAYERED && m.kind != EIG_MEDIUM_NODAL)
         return set_error(EIG_EINVAL, "medium kind");
@@ -1037,6 +1049,9 @@ int forward_solve_batch(eig_ctx* c, int32_t nsolve, const eig_grid* grid,
             wave.push_back(solves[i1]);
             ++i1;
         }
+        if (ws.bytes > c->budget &&
+            drop_side_table(c, grids[wave[0].grid], media[wave[0].medium]))
+            continue;
         int rc = ensure_ws(c, ws.bytes);
         if (rc) return rc;
         rc = run_wave(c, wave, grids, media, recsets, c->ws, c->ws_size, s);
@@ -1158,6 +1173,7 @@ static int jacobian_core(eig_ctx* c, int32_t nsample, const eig_grid* grid,
             need = wsz.bytes + extra + rwork;
             ++s1;
         }
+        if (need > c->budget && drop_side_table(c, grid[s0], media[med_of[s0]])) continue;
         int rc = ensure_ws(c, need);
         if (rc) return rc;
         // carve: [traces | sample descs | sigma given | sigma | per-sample
