@@ -70,13 +70,13 @@ int family_steps_of(const eig_ctx* c, int kind, bool one_step) {
 
 // Whether a solve with absorbing edges that is not resident streams several
 // steps per launch (variant 28): depth-only media with the side columns' table
-// (drop_side_table), forward solves, unless a variant, fewer steps per launch or
-// the separate edge kernel is asked for.
+// (drop_side_table), forward solves, where that variant is forced or neither
+// another one, fewer steps per launch nor the separate edge kernel is asked for.
 bool absorbing_stream(const eig_ctx* c, const SolveSpec& sp, const eig_grid& g,
                       const MediumKey& mk) {
     return g.bc == EIG_BC_ABSORBING && sp.rforce == nullptr && mk.ce &&
-           c->temporal_blocking == 4 && c->fused_edges &&
-           (c->forced_variant < 0 || c->forced_variant == kAbsorbingStream);
+           (c->forced_variant == kAbsorbingStream ||
+            (c->forced_variant < 0 && c->temporal_blocking == 4 && c->fused_edges));
 }
 
 // Leapfrog steps per launch of a tiled solve (a forced variant's, else its
