@@ -82,12 +82,13 @@ def _measured_traffic(solves_per_launch, wave_cache_bytes, variant):
     return rec["traffic_bytes_per_launch"] if rec else None
 
 
-# fields a four-step launch must move per update: each node's two levels
-# read once and written once per four steps (the tiles' halos, which
-# neighbouring tiles share, come mostly from L2); the streaming kernels
-# take eight (23) or six steps per launch
+# leapfrog steps per launch of the streaming kernels
+STREAM_STEPS = {23: 8, 24: 6, 28: 6}
+# fields a launch of four or more steps must move per update: each node's two
+# levels read once and written once per launch (the tiles' halos, which
+# neighbouring tiles share, come mostly from L2)
 BLOCKED_FLOOR_B = 32.0 / 4
-STREAM_FLOOR_B = {23: 32.0 / 8, 24: 32.0 / 6, 28: 32.0 / 6}
+STREAM_FLOOR_B = {v: 32.0 / k for v, k in STREAM_STEPS.items()}
 
 
 def _kernel_sources(variant, tiled):
@@ -97,12 +98,34 @@ def _kernel_sources(variant, tiled):
 
 
 def _steps_per_launch(variant):
-    """Leapfrog steps one launch of a stencil variant takes."""
+    """The temporal_blocking family of a stencil variant: its leapfrog steps per
+    launch, 4 where they are four or more."""
     if variant in (15, 16):
         return 3
-    if variant in (23, 24, 25, 26, 27, 28):   # the launch count's unit
+    if variant in (23, 24, 25, 26, 27, 28):
         return 4
     return 2 if (9 <= variant <= 14 or variant in (19, 20)) else 1
+
+
+def _kernel_steps(variant):
+    """Leapfrog steps one launch of a stencil variant takes."""
+    return STREAM_STEPS.get(variant, _steps_per_launch(variant))
+
+
+def _stats(ctx):
+    """The library's stencil figures since the last call, with the launches as
+    they were made (eig_ctx_stencil_stats counts them in units of four steps)."""
+    n = ctx.get_option("stencil_launches")
+    return dict(ctx.stencil_stats(reset=True), launches=n)
+
+
+def _valu_issue(variant, st):
+    """Fraction of the vector issue limit that the headline's stencil launches reach,
+    from the counter record's instructions per update, where it holds."""
+    rec = _counter_record(TRAFFIC_RECORD, _kernel_sources(variant, LAYERED_SOURCES),
+                          variant=variant)
+    per = rec.get("valu_lane_instr_per_update") if rec else None
+    return per * st["updates"] / (max(st["ms"], 1e-9) * 1e-3) / VALU_ISSUE_PEAK if per else None
 
 
 CPU_SHARE = 16   # host cores a one-GPU box grants a process
@@ -338,10 +361,11 @@ def _serving_c4(ctx, updates_per_s, max_updates=1.2e13, load=0.8, seed=3, overla
     return d
 
 
-def _leg_roofline(st, bytes_note, bound="hbm"):
-    """Stencil figures of one leg from the library's timing (eig_ctx_stencil_stats)."""
+def _leg_roofline(st, bytes_note, bound="hbm", floor_b=24.0):
+    """Stencil figures of one leg from the library's timing; floor_b: the bytes per
+    update that the leg's kernel must move (the library counts 24)."""
     ms = max(st["ms"], 1e-9)
-    achieved = st["bytes"] / (ms * 1e-3) / 1e9
+    achieved = st["bytes"] * floor_b / 24.0 / (ms * 1e-3) / 1e9
     return {"stencil_ms": st["ms"], "launches": st["launches"],
             "avg_launch_ms": st["ms"] / max(st["launches"], 1),
             "grid_pt_updates_per_s_stencil": st["updates"] / (ms * 1e-3),
@@ -387,7 +411,7 @@ def _bench_c3(nsample=4096, oracle_check=True):
                         status=status)
         torch.cuda.synchronize()
         t = time.perf_counter() - t0
-        st = ctx.stencil_stats(reset=True)
+        st = _stats(ctx)
         ws = ctx.workspace_bytes
         variant = ctx.get_option("last_variant")
     out = {"workload": f"uneven batch: {nsample} samples x 15 solves, grids "
@@ -396,15 +420,17 @@ def _bench_c3(nsample=4096, oracle_check=True):
            "grid_pt_updates_per_s": updates / t, "variant_last": variant,
            "workspace_GB": ws / 1e9, "flagged": int((status != 0).sum())}
     four = _steps_per_launch(variant) == 4
+    floor_b = STREAM_FLOOR_B.get(variant, BLOCKED_FLOOR_B) if four else 24.0
     out.update(_leg_roofline(
-        st, "24 B per grid-point update (read u^m, u^{m-1}, write u^{m+1}) over the stencil "
-            "launch time, against the 8 TB/s HBM peak; " +
-            ("eight steps per launch in registers, one wave per grid and length "
-             "through HBM: the kernel moves about 4 B per update, so achieved can pass "
-             "the peak" if four else
+        st, (f"{floor_b:.3g} B per grid-point update (both levels of a node in and out "
+             f"once per launch of {_kernel_steps(variant)} steps) over the stencil launch time, "
+             "against the 8 TB/s HBM peak; one wave per grid and length through HBM"
+             if four else
+             "24 B per grid-point update (read u^m, u^{m-1}, write u^{m+1}) over the stencil "
+             "launch time, against the 8 TB/s HBM peak; "
              "the waves run as cache-sized chunks, so the launches read and write the "
              "256 MB last-level cache (bound 'llc') and achieved may approach or pass the "
-             "HBM figure"), bound="hbm" if four else "llc"))
+             "HBM figure"), bound="hbm" if four else "llc", floor_b=floor_b))
     Hg = H1.cpu().numpy()
     seen = [k for k in picks if (np.diag(Hg[k]) > 0).all()]
     if oracle_check and seen:
@@ -475,7 +501,7 @@ def _bench_c5(reduced_grid=(512, 256, 1000), full_nodes=2, kmax=40, pipeline=Tru
                       w[order], sigma=sigma, per_receiver=True)
         torch.cuda.synchronize()
         t = time.perf_counter() - t0
-        st = ctx.stencil_stats(reset=True)
+        st = _stats(ctx)
         variant = ctx.get_option("last_variant")
         coef_interleave = ctx.get_option("coef_interleave")
         Hr = r["H1"].cpu().numpy()
@@ -492,7 +518,8 @@ def _bench_c5(reduced_grid=(512, 256, 1000), full_nodes=2, kmax=40, pipeline=Tru
             del rk
     upd = 15 * full_nodes * wl.grid.nx * wl.grid.nz * wl.grid.nsteps
     pts = wl.grid.nx * wl.grid.nz
-    shared = (24.0 * st["updates"] + 12.0 * pts * st["launches"]) / max(st["ms"], 1e-9) * 1e-6
+    floor_b = STREAM_FLOOR_B.get(variant, BLOCKED_FLOOR_B if variant >= 23 else 24.0)
+    shared = (floor_b * st["updates"] + 12.0 * pts * st["launches"]) / max(st["ms"], 1e-9) * 1e-6
     fs = {"grid": [wl.grid.nx, wl.grid.nz, wl.grid.nsteps],
           "sparse_grid_nodes_total": len(w), "nodes_run": full_nodes,
           "candidates": len(wl.receivers), "seconds": t, "variant_last": variant,
@@ -501,26 +528,37 @@ def _bench_c5(reduced_grid=(512, 256, 1000), full_nodes=2, kmax=40, pipeline=Tru
     leg = _leg_roofline(st, "")
     avg_ms = leg["avg_launch_ms"]
     solves_per_launch = round(st["updates"] / max(st["launches"], 1) /
-                              (pts * _steps_per_launch(variant)))
+                              (pts * _kernel_steps(variant)))
     rec = _counter_record(NODAL_TRAFFIC_RECORD, _kernel_sources(variant, NODAL_SOURCES),
                           variant=variant, solves_per_launch=solves_per_launch,
                           coef_interleave=coef_interleave)
     traffic = rec["traffic_bytes_per_launch"] if rec else None
     trate = traffic / (avg_ms * 1e-3) / 1e9 if traffic else None
     copy_gbs = _copy_rate()
+    issue = (rec["valu_lane_instr_per_update"] * st["updates"] / (max(st["ms"], 1e-9) * 1e-3) /
+             VALU_ISSUE_PEAK if rec else None)
+    alu = issue is not None and issue > trate / copy_gbs
+    peak = VALU_ISSUE_PEAK / 1e12 if alu else HBM_PEAK_GBS
+    achieved = issue * peak if alu else shared
     leg["roofline"] = {
-        "bound": "hbm", "achieved": shared, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-        "frac": shared / HBM_PEAK_GBS, "traffic": traffic, "traffic_rate_GBs": trate,
+        "bound": "alu" if alu else "hbm", "achieved": achieved, "peak": peak,
+        "unit": "10^12 vector lane-instructions/s" if alu else "GB/s",
+        "frac": achieved / peak, "achieved_GBs": shared,
+        "traffic": traffic, "traffic_rate_GBs": trate,
         "copy_GBs_measured": copy_gbs,
-        "frac_of_copy": trate / copy_gbs if trate else None,
+        "frac_of_copy": trate / copy_gbs if trate else None, "valu_issue_frac": issue,
         "achieved_36B_per_update_GBs": 36.0 * st["updates"] / (max(st["ms"], 1e-9) * 1e-3) / 1e9,
-        "note": "achieved: 24 B of fields per grid-point update plus the medium's 12 B of "
-                "nodal lambda, mu, dt^2/(rho h^2) per grid point once per launch (the "
+        "note": f"achieved_GBs: {floor_b:.3g} B of fields per grid-point update (both levels in "
+                f"and out once per launch of {_kernel_steps(variant)} steps) plus the medium's "
+                "12 B of nodal lambda, mu, dt^2/(rho h^2) per grid point once per launch (the "
                 f"{solves_per_launch} solves of a launch share one medium); the 36 B-per-"
-                "update unit (achieved_36B_per_update_GBs) counts those coefficients once "
-                "per solve and so overstates the bytes.  traffic: bytes per launch past L2 "
+                "update unit (achieved_36B_per_update_GBs) counts one step's fields and those "
+                "coefficients once per solve.  traffic: bytes per launch past L2 "
                 "(FETCH_SIZE + WRITE_SIZE, copy-calibrated) from the counter record; "
-                "frac_of_copy: that rate over a plain 4 GiB copy measured here"}
+                "frac_of_copy: that rate over a plain 4 GiB copy measured here; "
+                "valu_issue_frac: the record's vector lane-instructions per update times the "
+                "update rate over the 3.93e13/s issue limit.  bound, achieved: the larger of "
+                "the two"}
     fs.update(leg)
     if gold is not None:
         from oracle import laplace
@@ -618,7 +656,7 @@ def _bench_c5_full_query(batch=30, kmax=40):
         ctx.design_greedy(H, make_prior(wl.lo, wl.hi), w, kmax, order, curve, theta=nodes)
         torch.cuda.synchronize()
         t_greedy = time.perf_counter() - t1
-        st = ctx.stencil_stats(reset=True)
+        st = _stats(ctx)
     upd = 15.0 * S * wl.grid.nx * wl.grid.nz * wl.grid.nsteps
     cv = curve.cpu().numpy()
     return {"workload": "c5 at full size: 2048x1024x4000 nodal medium, level-3 sparse grid "
@@ -678,7 +716,7 @@ def _bench_model(nmc=10000, ncheck=2):
             ctx.design_eval(H, dmask, prior, wl.weights, e, theta=wl.theta)
             torch.cuda.synchronize()
             t = time.perf_counter() - t0
-            st = ctx.stencil_stats(reset=True)
+            st = _stats(ctx)
             variant = ctx.get_option("last_variant")
             nsol = 15 if jac == "fd" else 8
             upd_s = st["updates"] / (max(st["ms"], 1e-9) * 1e-3)
@@ -792,7 +830,7 @@ def _bench_loh2d(ctx, nmc=10000, level=5, nbatch=10):
         H, st = per_receiver_h1(wl.theta, jac)
         torch.cuda.synchronize()
         t = time.perf_counter() - t0
-        sst = ctx.stencil_stats(reset=True)
+        sst = _stats(ctx)
         nsol = 15 if jac == "fd" else 8
         upd = nsol * nmc * wl.grid.nx * wl.grid.nz * wl.grid.nsteps
         eig = design_eigs(H, wl.theta, wl.weights)
@@ -1126,7 +1164,7 @@ def main():
         out = run_query(ctx, g, med, wl.receivers, wl.lo, wl.hi, wl.theta, wl.weights,
                         sigma=sigma)
         if record:
-            st = ctx.stencil_stats(reset=True)
+            st = _stats(ctx)
             for k in jac_stats:
                 jac_stats[k] += st[k]
         return out
@@ -1155,12 +1193,17 @@ def main():
     total_ms = ev[0].elapsed_time(ev[-1])
     st = jac_stats
     variant = ctx.get_option("last_variant")
-    steps_per_launch = _steps_per_launch(variant)
+    steps_per_launch = _kernel_steps(variant)
     S = len(wl.theta)
     value = S * args.steps / (total_ms / 1e3)
     avg_launch_ms = st["ms"] / max(st["launches"], 1)
     bytes_per_launch = st["bytes"] / max(st["launches"], 1)
-    achieved = bytes_per_launch / (avg_launch_ms / 1e3) / 1e9
+    in_cache = steps_per_launch < 4   # two or three steps: cache-sized chunks
+    floor_b = {1: 24.0, 2: 16.0, 3: 32.0 / 3.0}.get(
+        steps_per_launch, STREAM_FLOOR_B.get(variant, BLOCKED_FLOOR_B))
+    algorithmic = bytes_per_launch / (avg_launch_ms / 1e3) / 1e9   # 24 B per update
+    # launches of four or more steps cannot move 24 B per update: their own floor
+    achieved = algorithmic if in_cache else algorithmic * floor_b / 24
     dkl = out["dkl"].cpu().numpy()
     eig = float(out["eig"].cpu()[0])
     copy_gbs = _copy_rate()
@@ -1170,8 +1213,7 @@ def main():
     traffic = _measured_traffic(round(solves_per_launch), ctx.get_option("wave_cache_bytes"),
                                 variant)
     traffic_rate = traffic / (avg_launch_ms * 1e-3) / 1e9 if traffic else None
-    in_cache = steps_per_launch < 4   # two or three steps: cache-sized chunks
-    floor_b = {1: 24.0, 2: 16.0, 3: 32.0 / 3.0, 4: STREAM_FLOOR_B.get(variant, BLOCKED_FLOOR_B)}[steps_per_launch]
+    issue = _valu_issue(variant, st)
     status_ok = int(out["status"].abs().sum()) == 0 and int(out["chol_status"].abs().sum()) == 0
     line = {
         "metric": METRIC,
@@ -1200,19 +1242,19 @@ def main():
                     "variant": variant, "steps_per_launch": steps_per_launch,
                     "bytes_per_launch": bytes_per_launch,
                     "kernel_floor_bytes_per_update": floor_b,
-                    "achieved_at_kernel_floor_GBs": achieved * floor_b / 24,
+                    "achieved_at_kernel_floor_GBs": algorithmic * floor_b / 24,
+                    "achieved_24B_per_update_GBs": algorithmic,
                     "time_frac_of_step": st["ms"] / total_ms,
                     "solves_per_launch": solves_per_launch,
                     "note": ("launches of the 15*S-solve jacobian_fd wave, every solve in "
-                             "every launch (eight steps per launch, streamed through "
-                             "registers and counted as two launches of four steps: the "
+                             f"every launch ({steps_per_launch} steps per launch: the "
                              "fields stream through HBM)"
                              if not in_cache else
                              "launches of the 15*S-solve jacobian_fd wave, run as chunks "
                              "whose fields (4 buffers per solve) fit wave_cache_bytes, so "
                              "they stay in the 256 MB last-level cache between launches") +
-                            "; bytes_per_launch and roofline.achieved count 24 B per "
-                            "grid-point update (read u^m, u^{m-1}, write u^{m+1}); "
+                            "; bytes_per_launch and achieved_24B_per_update_GBs count 24 B "
+                            "per grid-point update (read u^m, u^{m-1}, write u^{m+1}); "
                             "kernel_floor_bytes_per_update: what the kernel itself must "
                             "move per update (achieved_at_kernel_floor_GBs)"},
         "latency_ms": {"p50": float(np.percentile(lat, 50)),
@@ -1226,18 +1268,22 @@ def main():
                      "copy_GBs_measured": copy_gbs,
                      "frac_of_copy": (traffic_rate / copy_gbs
                                       if traffic_rate and not in_cache else None),
+                     "valu_issue_frac": issue,
                      "wave_cache_bytes": ctx.get_option("wave_cache_bytes"),
-                     "note": "achieved: 24 B per update (algorithmic: read u^m, u^{m-1}, "
-                             "write u^{m+1}) over the launch time; frac: achieved / the "
-                             "8 TB/s HBM peak. " + (
-                                 "The kernel takes eight steps per launch in registers, "
-                                 "so it moves about 4 B per update, not 24: "
-                                 "achieved can pass the peak. traffic: bytes per launch "
+                     "note": "frac: achieved / the 8 TB/s HBM peak. " + (
+                                 f"achieved: {floor_b:.3g} B per update (both levels of a "
+                                 "node in and out once per launch) over the launch time. "
+                                 "traffic: bytes per launch "
                                  "past L2 from the counter record; frac_of_copy: that "
                                  "traffic rate over a plain 2 x 4 GiB copy measured in "
-                                 "this run (copy_GBs_measured). two_step_llc: the same "
-                                 "query with two steps per launch in cache-sized chunks"
+                                 "this run (copy_GBs_measured); valu_issue_frac: the "
+                                 "record's vector lane-instructions per update times the "
+                                 "update rate over the 3.93e13/s issue limit.  Memory is the "
+                                 "nearer of the two, and neither is reached. two_step_llc: the "
+                                 "same query with two steps per launch in cache-sized chunks"
                                  if not in_cache else
+                                 "achieved: 24 B per update (algorithmic: read u^m, u^{m-1}, "
+                                 "write u^{m+1}) over the launch time. "
                                  "The launches work in the 256 MB last-level cache "
                                  "(cache-sized chunks), so the bound is that cache; "
                                  "traffic: bytes per launch past L2 from the counter record; "
@@ -1263,14 +1309,14 @@ def main():
     ou = one_step()
     e1.record(stream)
     torch.cuda.synchronize()
-    stu = ctx.stencil_stats(reset=True)
+    stu = _stats(ctx)
     tu = e0.elapsed_time(e1) / 1e3
     vu = ctx.get_option("last_variant")
     ctx.set_option("temporal_blocking", tb0)
     ach_u = stu["bytes"] / (stu["ms"] * 1e-3) / 1e9
     line["two_step_llc" if other_tb == 2 else "four_step_hbm"] = {
         "value": S / tu, "unit": "sample-EIG evals/s", "variant": vu,
-        "steps_per_launch": _steps_per_launch(vu),
+        "steps_per_launch": _kernel_steps(vu),
         "avg_launch_ms": stu["ms"] / max(stu["launches"], 1),
         "launches": stu["launches"],
         "grid_pt_updates_per_s_stencil": stu["updates"] / (stu["ms"] * 1e-3),

@@ -144,9 +144,10 @@ const char* eig_last_error(void);
 size_t eig_ctx_workspace_bytes(const eig_ctx* ctx);
 /* Stencil timing since the last reset: device time from the first to the
  * last stencil launch of every wave (HIP events on the call's stream), the
- * number of stencil launches (a launch of more than four steps counts as the
- * four-step launches it stands for), the grid-point updates they performed
- * (sum over solves of nx*nz per step) and their algorithmic HBM bytes (per
+ * number of stencil launches in units of at most four steps (a longer launch
+ * counts as the four-step launches that its steps would take; the option
+ * "stencil_launches" below counts them as they are), the grid-point updates
+ * they performed (sum over solves of nx*nz per step) and their algorithmic HBM bytes (per
  * update: read u^m and u^{m-1}, write u^{m+1}, 8 bytes each; plus 12 bytes
  * of nodal coefficients for EIG_MEDIUM_NODAL).  Waits for the recorded
  * events.  Any output pointer may be NULL; reset != 0 clears the counters
@@ -220,7 +221,8 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
  * EIG_EINVAL for an unknown name or value. */
 int eig_ctx_set_option(eig_ctx* ctx, const char* name, int64_t value);
 /* Reads an option back; "last_variant" gives the stencil variant of the most
- * recent launch.  "temporal_blocking": leapfrog steps per launch for media
+ * recent launch, "stencil_launches" the number of stencil kernel launches since
+ * eig_ctx_stencil_stats was last reset.  "temporal_blocking": leapfrog steps per launch for media
  * with rigid edges, 4 (default: four or more; variants 23 and, nodal media, 24:
  * eight and six steps streamed through registers; for small launches 26 and
  * 27: four with the tile and its halo in LDS, 25 a forced-only form of 27;

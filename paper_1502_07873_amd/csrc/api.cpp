@@ -692,6 +692,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
                     !(kVariants[g.cand[vi]].edges && c->fused_edges))
                     launch_ce_edges(ddesc + g.first, nrun, step, ls);
                 c->launches += launch_units(kVariants[g.cand[vi]], step, stv.front().first);
+                c->kernel_launches += 1;
                 c->updates += upd;
                 c->bytes += upd * (g.kind == EIG_MEDIUM_NODAL ? 36.0 : 24.0);
             }
@@ -950,6 +951,7 @@ int eig_ctx_get_option(const eig_ctx* c, const char* name, int64_t* value) {
     else if (n == "graph_captures") *value = c->graph_captures;
     else if (n == "graph_replays") *value = c->graph_replays;
     else if (n == "last_variant") *value = c->last_variant;
+    else if (n == "stencil_launches") *value = c->kernel_launches;
     else return set_error(EIG_EINVAL, "unknown option " + n);
     return EIG_OK;
 }
@@ -974,6 +976,7 @@ int eig_ctx_stencil_stats(eig_ctx* c, int32_t reset, double* ms, int64_t* launch
     if (reset) {
         c->resolved_ms = 0.0;
         c->launches = 0;
+        c->kernel_launches = 0;
         c->updates = 0.0;
         c->bytes = 0.0;
     }

@@ -50,7 +50,8 @@ struct eig_ctx {
     int stage_next = 0;
     // stencil timing: event pairs per wave, launch / update / byte counters
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timing;
-    int64_t launches = 0;
+    int64_t launches = 0;         // in units of at most four steps (launch_units)
+    int64_t kernel_launches = 0;  // as launched
     double updates = 0.0, bytes = 0.0;
     double resolved_ms = 0.0;
     // stencil variant selection: forced (EIG_STENCIL_VARIANT), or tuned
@@ -187,10 +188,10 @@ inline bool deviation_in_window(double coord, double step, double h) {
     return std::abs(a - b) <= kSrcW - 6;
 }
 
-// What launch number `step` of a solve group counts as in the launch
-// statistics: four-step launches where the streaming kernels run (each takes
-// the place of the four-step launches of its steps; nmax: the group's longest
-// solve), one otherwise.
+// What launch number `step` of a solve group counts as in eig_ctx_stencil_stats'
+// launches: the launches of at most four steps that its steps would take (nmax:
+// the group's longest solve).  Option "stencil_launches" counts launches as they
+// are.
 inline int64_t launch_units(const StencilVariant& v, int64_t step, int64_t nmax) {
     if (!v.stream) return 1;
     auto four = [&](int64_t launches) { return (std::min(launches * v.steps, nmax) + 3) / 4; };

@@ -773,9 +773,12 @@ int eig_server_step(eig_server* v, int32_t max_launches, void* stream, int32_t* 
         }
         for (int64_t l = 0; l < seg; ++l) {
             double upd = 0.0;
+            int64_t units[kNumVariants] = {};  // what a variant's launch counts as
             for (auto& gr : v->groups) {
                 if (!gr.on) continue;
                 const int spl = spl_of(gr);
+                int64_t& n = units[gr.variant];
+                n = std::max(n, launch_units(kVariants[gr.variant], gr.done, gr.nsteps));
                 const int64_t left = gr.nsteps - spl * gr.done;
                 upd += (double)gr.q->grid.nx * gr.q->grid.nz * gr.nslot *
                        (double)std::min<int64_t>(spl, left);
@@ -789,7 +792,8 @@ int eig_server_step(eig_server* v, int32_t max_launches, void* stream, int32_t* 
                 if (kt.ntiles == 0) continue;
                 launch_stencil(v->descs, v->tiles + v->kind_tile_off[kk], (int)kt.ntiles,
                                (int)v->launch, kt.variant, kt.rows, s);
-                c->launches += kVariants[kt.variant].stream ? kVariants[kt.variant].steps / 4 : 1;
+                c->launches += units[kt.variant];
+                c->kernel_launches += 1;
             }
             ++v->launch;
         }
