@@ -221,8 +221,9 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
  * EIG_EINVAL for an unknown name or value. */
 int eig_ctx_set_option(eig_ctx* ctx, const char* name, int64_t value);
 /* Reads an option back; "last_variant" gives the stencil variant of the most
- * recent launch, "stencil_launches" the number of stencil kernel launches since
- * eig_ctx_stencil_stats was last reset.  "temporal_blocking": leapfrog steps per launch for media
+ * recent launch, "last_strip" the columns per strip (128, two per lane, or 64) of
+ * the most recent launch that streams strips, "stencil_launches" the number of
+ * stencil kernel launches since eig_ctx_stencil_stats was last reset.  "temporal_blocking": leapfrog steps per launch for media
  * with rigid edges, 4 (default: four or more; variants 23 and, nodal media, 24:
  * eight and six steps streamed through registers; for small launches 26 and
  * 27: four with the tile and its halo in LDS, 25 a forced-only form of 27;

@@ -671,6 +671,7 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
             }
             if (ntile > 0) {
                 c->last_variant = g.cand[vi];
+                if (kVariants[g.cand[vi]].stream) c->last_strip = g.cut.narrow ? 64 : 128;
                 if (slot >= 0) HIP_TRY(hipEventRecord(tn.ev[2 * slot], s));
                 if (spl == 3 && !replay) {
                     int nh = 0;
@@ -951,6 +952,7 @@ int eig_ctx_get_option(const eig_ctx* c, const char* name, int64_t* value) {
     else if (n == "graph_captures") *value = c->graph_captures;
     else if (n == "graph_replays") *value = c->graph_replays;
     else if (n == "last_variant") *value = c->last_variant;
+    else if (n == "last_strip") *value = c->last_strip;
     else if (n == "stencil_launches") *value = c->kernel_launches;
     else return set_error(EIG_EINVAL, "unknown option " + n);
     return EIG_OK;

@@ -64,6 +64,7 @@ struct eig_ctx {
     bool autotune = true;
     std::map<std::tuple<int, int, int, int, int>, int> tuned;
     int last_variant = -1;  // variant of the most recent stencil launch
+    int last_strip = 0;     // columns per strip of the most recent streaming one
     int64_t max_wave_solves = 0;  // 0: no limit (all solves of a wave per launch)
     // live field bytes per wave chunk (0: no limit); 192 MiB leaves room in
     // the device's 256 MB last-level cache for everything else a launch reads
