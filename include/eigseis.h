@@ -214,24 +214,26 @@ int eig_ctx_stencil_stats(eig_ctx* ctx, int32_t reset, double* ms, int64_t* laun
  *   "fused_edges"      1 (default): the two-nodes-per-lane one-step kernels
  *                      update absorbing edge nodes in extra wavefronts of
  *                      their own launch; 0: a separate edge kernel after each
- *                      launch (and one step per launch).  Same results either
- *                      way.
+ *                      launch (and one step per launch, unless variant 28 is
+ *                      forced).  Same results either way.
  *   "max_wave_solves"  0 (default): no limit; n > 0: at most n solves per
  *                      launch (n = 1 is the plain one-solve-at-a-time path)
  * EIG_EINVAL for an unknown name or value. */
 int eig_ctx_set_option(eig_ctx* ctx, const char* name, int64_t value);
 /* Reads an option back; "last_variant" gives the stencil variant of the most
- * recent launch, "last_strip" the columns per strip (128, two per lane, or 64) of
- * the most recent launch that streams strips, "stencil_launches" the number of
- * stencil kernel launches since eig_ctx_stencil_stats was last reset.  "temporal_blocking": leapfrog steps per launch for media
- * with rigid edges, 4 (default: four or more; variants 23 and, nodal media, 24:
- * eight and six steps streamed through registers; for small launches 26 and
- * 27: four with the tile and its halo in LDS, 25 a forced-only form of 27;
- * forward solves of depth-only media with absorbing edges 28: six), 2 (1 also selects 2), 3
- * (depth-only media; nodal media then take two), or 0 for one step; two to
- * four steps per launch keep four field buffers per solve.  Serving engines
- * created while it is 4 run those variants for both media; otherwise two for
- * depth-only media and one for nodal media. */
+ * recent launch, "last_strip" the columns per strip (128, two per lane, or 64)
+ * of the most recent launch that streams strips, "stencil_launches" the number
+ * of stencil kernel launches since eig_ctx_stencil_stats was last reset.
+ * "temporal_blocking": leapfrog steps per launch for media with rigid edges, 4
+ * (default: four or more; variants 23 and, nodal media, 24: eight and six steps
+ * streamed through registers; for small launches 26 and 27: four with the tile
+ * and its halo in LDS, 25 a forced-only form of 27; forward solves of depth-only
+ * media with absorbing edges 28: six, but one step for a solve that the budget
+ * holds only without that kernel's 16 B per row), 2 (1 also selects 2), 3
+ * (depth-only media; nodal media then take two), or 0 for one step; two to four
+ * steps per launch keep four field buffers per solve.  Serving engines created
+ * while it is 4 run those variants for both media; otherwise two for depth-only
+ * media and one for nodal media. */
 int eig_ctx_get_option(const eig_ctx* ctx, const char* name, int64_t* value);
 
 /*
@@ -445,6 +447,11 @@ int design_eval(eig_ctx* ctx, int32_t nsample, int32_t ncand, const double* H1r,
  * never chosen.  The search stays on the device.
  *   order: device int32 [kmax] (chosen candidate per step, -1 once none is
  *          left); curve: device [kmax] (I after each step, NaN after -1).
+ * Workspace: 8 * nsample * (ncand + 57) + 8 * ncand bytes at least.  Where the
+ * context's budget has room for 8 n (n + 1) / 2 bytes more per sample and
+ * candidate (n inferred parameters), they hold a packed copy of H1r, which is
+ * faster to read; like any growth of the workspace (by a quarter more than asked
+ * for, up to the budget) it is kept until the context is destroyed.
  */
 int design_greedy(eig_ctx* ctx, int32_t nsample, int32_t ncand,
                   const double* H1r, const eig_prior* prior, const double* theta,

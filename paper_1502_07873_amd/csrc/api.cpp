@@ -252,7 +252,8 @@ int run_chunk(eig_ctx* c, const std::vector<SolveSpec>& solves,
     std::sort(rec_used.begin(), rec_used.end());
     rec_used.erase(std::unique(rec_used.begin(), rec_used.end()), rec_used.end());
     std::map<int, size_t> med_off;
-    for (int m : med_used) med_off[m] = cv.take(medium_bytes(media[m])) + medium_table(media[m].kind);
+    for (int m : med_used)
+        med_off[m] = cv.take(medium_bytes(media[m])) + medium_table(media[m].kind);
     // stencil variants this wave may use, per solve class (medium kind,
     // absorbing edges, dual solve): the last two need one step per launch
     std::vector<int> cands[2][2];

@@ -186,7 +186,7 @@ void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int s
 // Tiled depth-only variants (0..5, 7..16) of launch_stencil.
 void launch_layered_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int step,
                             int variant, hipStream_t s);
-// Variants 26 (depth-only) and 24, 25 (nodal) of launch_stencil: K steps
+// Variants 26 (depth-only) and 25, 27 (nodal) of launch_stencil: K steps
 // per launch with the tile in LDS, one workgroup per tile.
 void launch_blocked_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int pass,
                             int variant, hipStream_t s);

@@ -198,7 +198,9 @@ __device__ __forceinline__ double log_prior(const eig_prior& pr, const Active<N>
     return -0.5 * q - 0.5 * (N * log(2.0 * M_PI) + ld);
 }
 
-__device__ __forceinline__ double quiet_nan() { return __longlong_as_double(0x7ff8000000000000ULL); }
+__device__ __forceinline__ double quiet_nan() {
+    return __longlong_as_double(0x7ff8000000000000ULL);
+}
 
 // Theorem 4 on the inferred parameters' block of H_1 (overwritten); lp =
 // h(theta).  NaN if the block is not positive definite.
@@ -215,10 +217,10 @@ __device__ __forceinline__ double dkl_of(double (&h)[kTri<N>], double lp, double
 //   -1/2 log((2 pi)^N |H^-1|) - N/2 - h(theta^) - 1/2 tr(H^-1 grad grad h),
 // grad grad h = 0 for the uniform prior and -Gamma^-1 for the Gaussian one.
 template <int N>
-__global__ void __launch_bounds__(64) theorem3_kernel(const double* __restrict__ H1, const double* __restrict__ H2,
-                                int nsample, const eig_prior* __restrict__ prior,
-                                const double* __restrict__ theta, double* __restrict__ val,
-                                int32_t* __restrict__ status) {
+__global__ void __launch_bounds__(64)
+theorem3_kernel(const double* __restrict__ H1, const double* __restrict__ H2, int nsample,
+                const eig_prior* __restrict__ prior, const double* __restrict__ theta,
+                double* __restrict__ val, int32_t* __restrict__ status) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= nsample) return;
     const eig_prior& pr = *prior;

@@ -270,7 +270,7 @@ __device__ __forceinline__ void lds_put(float2* p, const Pt<N>& w) {
 
 // Edge node e (ce_edge_pos), u^m in LDS buffer half par, u^{m-1} in the other one,
 // which takes u^{m+1}.  The relation of ce.h, its quotients as products with the
-// FP64 reciprocals (the same bits).  last: the wave that owns row nz-2.
+// FP64 reciprocals (the same bits, as absorbing_columns says).  last: the wave that owns row nz-2.
 template <int N>
 __device__ __forceinline__ void resident_edge(const ResSolve& g, int par, int e, int last) {
 #pragma clang fp contract(off)
@@ -481,7 +481,8 @@ __device__ __forceinline__ void resident_run(const ResSolve& g) {
 
 // Sets up LDS and runs the grid's instance.
 template <bool WIDE>
-__device__ __forceinline__ void resident_registers(const SolveDesc* d, bool absorbing, float4* lds) {
+__device__ __forceinline__ void resident_registers(const SolveDesc* d, bool absorbing,
+                                                   float4* lds) {
     ResSolve g;
     g.d = d;
     g.coef = d->coef;
@@ -502,7 +503,8 @@ __device__ __forceinline__ void resident_registers(const SolveDesc* d, bool abso
     g.inner = g.side + 2 * g.nz;
     float2* srcw = g.rows + 2 * g.half;
     EdgeRow* edge = (EdgeRow*)(srcw + 64);
-    for (int j = threadIdx.x; j < g.half; j += kResThreads) lds[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = threadIdx.x; j < g.half; j += kResThreads)
+        lds[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (threadIdx.x < 64) {
         const int dk = threadIdx.x / 8, di = threadIdx.x % 8;
         float2 x = make_float2(0.f, 0.f);

@@ -19,10 +19,12 @@
 // path (the surface, the forcing window, past the last free row) branch to
 // stream_special; the branch is uniform.
 //
-// Bound: vector issue.  An update takes 24 vector instructions (13 per
-// component, the depth differences shared between rows) times the overlap
-// (1.13 at 512 columns) and the halo rows; past L2 a launch moves each node's
-// two levels once in and once out, 4 B per update.  K = 8 is what 256 VGPRs
+// Bound: memory and vector issue together.  On 3840 solves of 512^2 the fields
+// move at 0.85 of the rate of a large copy, and the SIMDs issue vector instructions
+// in 0.81 of the cycles (2.26 GHz under this load).  An update takes 24 vector
+// instructions (13 per component, the depth differences shared between rows) times
+// the overlap (1.13 at 512 columns) and the halo rows; past L2 a launch moves each
+// node's two levels once in and once out, 4 B per update.  K = 8 is what 256 VGPRs
 // hold, two waves per SIMD; measured on 240 solves of 512^2 in the Monte Carlo
 // query: K = 4 336 ms, 6 244 ms, 8 211 ms.  On 960 solves of 512^2: 9.5e11
 // updates/s against 4.9e11 for four steps with the tile in LDS (67 instructions
@@ -72,10 +74,12 @@ struct AbsorbingSides {
 // The side columns of an absorbing strip (the relation of ce.h, ce_side):
 // `below` and `above` are the column's rows r + 1 and r - 1 and half 1/2 (at the
 // ends of a side column: the one-sided difference and 1).  x / (1 + a) is x
-// times the FP64 reciprocal, rounded to FP32: the bits of the FP32 division,
-// because a quotient of two FP32 numbers is no closer than 2^-48 of itself to
-// where the rounding changes, and the product is off by 2^-52.  It takes 3
-// instructions, a division 10.
+// times the FP64 reciprocal, rounded to FP32: the bits of the FP32 division.
+// The product is off by 2^-52 of itself.  A quotient of two FP32 numbers that is
+// not exactly where the rounding changes is at least 2^-48 of itself away,
+// subnormal results included; exactly there it is only where a subnormal result's
+// divisor is 2 (whose reciprocal is exact) or above 4, and 1 + a is below 2 for
+// every stable time step.  It takes 3 instructions, a division 10.
 template <int K, int N, class S>
 __device__ __forceinline__ void absorbing_columns(const StreamTile<K, N>& t, const CeRow& ce,
                                                   float half, const Pt<N>& below,
@@ -224,7 +228,8 @@ __device__ __forceinline__ void stream_row(const StreamTile<K, N>& t, StreamStat
             zero_rigid<K, N>(t, nw);
         }
         if (__builtin_expect(!plain, 0))
-            stream_special<K, N, S>(t, j, r, ci - j * kCoefStride, cf, ce, n, c, p, s.dc[j - 1], up, a, nw);
+            stream_special<K, N, S>(t, j, r, ci - j * kCoefStride, cf, ce, n, c, p, s.dc[j - 1],
+                                    up, a, nw);
         if (j == K && (unsigned)(r - t.kb) < (unsigned)t.nstore && t.st_ok) {
             Pt<N> w1 = c, w0 = nw;
             if constexpr (S::kAbs && N == 2) {
@@ -304,7 +309,7 @@ stencil_layered_stream(const SolveDesc* __restrict__ descs, const int2* __restri
 // edge).  What a strip has of the sides is its template, so that the inner
 // strips and each kind of side strip pay for what they hold only; the side
 // columns take 16 instructions a side and level for both components, against
-// 24 per update of all 128 columns.  Bound: vector issue, as above.  K = 6: 8
+// 24 per update of all 128 columns.  Bound: vector issue.  K = 6: 8
 // spills registers.  Against one step per launch (edge nodes in extra
 // wavefronts; launch-bound up to some 60 solves of 252 x 90, field bytes above),
 // us per step on 252 x 90: 1 solve 8.9 -> 4.4, 30 9.3 -> 6.2, 60 10.6 -> 9.4, 104

@@ -14,9 +14,11 @@
 //
 // Bound: vector issue, 50 instructions per update before the strips' overlap and
 // the halo rows (63 counted on 512 x 256; the kernel with tile and medium in
-// LDS 144, most of it LDS addresses, operand copies and band set-up), at 0.70 of
-// the issue limit there.  K = 6 is what 256 VGPRs hold, and only if lambda D_x u
-// of the row above is formed a second time when needed (held, it spills).
+// LDS 144, most of it LDS addresses, operand copies and band set-up): at 0.70 of
+// the issue limit there, and on 30 solves of 2048 x 1024 in 0.85 of the cycles, with
+// memory at 0.6 of a large copy's rate.  K = 6 is what 256 VGPRs hold, and only if
+// lambda D_x u of the row above is formed a second time when needed (held, it
+// spills).
 // Measured, against four steps with the tile in LDS: 15 solves of 2048 x 1024
 // 4.7e11 updates/s against 2.7e11 (K = 4: 4.7e11), 360 of 512 x 256 4.5e11
 // against 2.9e11 (4.4e11), 960 of 512^2 5.6e11 against 2.9e11 (5.0e11); small
@@ -307,7 +309,8 @@ __device__ __forceinline__ void ld_coef(const float* row, size_t plane, int col,
 }
 
 template <int K, int N, bool EDGE>
-__device__ __forceinline__ void nodal_strip(const StreamEntry& e, const float* sw, int* rec, float* mem) {
+__device__ __forceinline__ void nodal_strip(const StreamEntry& e, const float* sw, int* rec,
+                                            float* mem) {
     StreamTile<K, N> t;
     tile_init<K, N>(t, e.d, e.m, e.pin, e.x0, e.kb, e.ke, sw, rec);
     const float h2 = e.d->h2;

@@ -58,9 +58,9 @@ void launch_stencil(const SolveDesc* descs, const int2* tiles, int ntiles, int s
 }
 
 // A launch's time in the units of one wide row (K levels of 128 columns) on a
-// SIMD of its own, 1.0 us (nodal media 1.44 us): a wave takes rows + 2 K of them, a narrow row 0.65,
-// and two waves of a SIMD slow each other down 1.65 times (measured per launch
-// over 15 to 960 solves of 128 to 512 columns).  Up to the chip's 2048 waves
+// SIMD of its own, 1.0 us (nodal media 1.44 us): a wave takes rows + 2 K of them, a
+// narrow row 0.65, and two waves of a SIMD slow each other down 1.65 times (measured
+// per launch over 15 to 960 solves of 128 to 512 columns).  Up to the chip's 2048 waves
 // (two per SIMD) a launch takes as long as one wave; a few more wait for a
 // whole further one; from 1.25 rounds on the waves' ends are spread enough for
 // the work to count, and half a wave for the end.
@@ -101,16 +101,16 @@ StreamCut stream_cut(int v, const std::vector<StreamLoad>& all) {
     return best;
 }
 
-// Launches of few tiles take four steps with the tile in LDS instead: its 8
-// waves share the tile's rows (58 x 58 nodes, nodal media 58 x 34), while a
-// streaming wave takes its rows one after the other however few waves there
-// are.  Both estimates in us per eight steps (the LDS kernels' two launches; the
-// streaming ones' rows, and 19 us per launch for their start and their rows on
-// the window and the surface).  Measured, LDS against streaming, depth-only: 1 solve of 512^2 (81 tiles) 26 / 36, 30 of 200 x 150
-// (360) 36 / 48, 60 of 300 x 90 (720) 60 / 63, 60 of four uneven grids (915)
-// 69 / 80, 15 of 512^2 (1215) 84 / 84, 120 of 128^2 (1080) 66 / 63, 60 of 384^2
-// (2940) 178 / 134, 105 of 256^2 (2625) 144 / 119; nodal: 1 of 512^2 (144) 24 /
-// 41, 30 of 200 x 150 (600) 50 / 58, 30 of 300 x 200 (1080) 76 / 82, 120 of
+// Launches of few tiles take four steps with the tile in LDS instead: its 8 waves
+// share the tile's rows (58 x 58 nodes, nodal media 58 x 34), while a streaming wave
+// takes its rows one after the other however few waves there are.  Both estimates in
+// us per eight steps (the LDS kernels' two launches; the streaming ones' rows, and
+// 19 us per launch for their start and their rows on the window and the surface).
+// Measured, LDS against streaming, depth-only: 1 solve of 512^2 (81 tiles) 26 / 36,
+// 30 of 200 x 150 (360) 36 / 48, 60 of 300 x 90 (720) 60 / 63, 60 of four uneven
+// grids (915) 69 / 80, 15 of 512^2 (1215) 84 / 84, 120 of 128^2 (1080) 66 / 63, 60
+// of 384^2 (2940) 178 / 134, 105 of 256^2 (2625) 144 / 119; nodal: 1 of 512^2 (144)
+// 24 / 41, 30 of 200 x 150 (600) 50 / 58, 30 of 300 x 200 (1080) 76 / 82, 120 of
 // 128^2 (1440) 85 / 77, 90 of 300 x 200 (3240) 169 / 147.
 int small_launch_variant(int v, const std::vector<StreamLoad>& loads) {
     const int lds = kVariants[v].medium_kind == EIG_MEDIUM_NODAL ? 27 : 26;
