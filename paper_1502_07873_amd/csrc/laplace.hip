@@ -67,11 +67,12 @@ __device__ __forceinline__ bool scaled_logdet(double (&a)[kTri<N>], double* out)
     // Rows with a diagonal entry far down the range, the subnormals among them,
     // are brought up by 2^256 each first (exactly): 1 / (s_i s_j) would overflow
     // from s_i s_j = 2^-1024 on.
+    // Compared by their high words, whose minimum is an instruction each.
     constexpr double kFarDown = 0x1p-960;
-    bool far = false;
+    int low = __double2hiint(a[0]);
 #pragma unroll
-    for (int j = 0; j < N; ++j) far = far || a[tri(j, j)] < kFarDown;
-    if (__builtin_expect(far, 0)) {
+    for (int j = 1; j < N; ++j) low = min(low, __double2hiint(a[tri(j, j)]));
+    if (__builtin_expect(low < __builtin_bit_cast(int64_t, kFarDown) >> 32, 0)) {
         int up[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) {
